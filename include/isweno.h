@@ -347,10 +347,10 @@ ISWENO_API int isweno_timing_read(isweno_ctx *ctx, int kind, double *total_ms,
 
 /* Field-sides per axis (counts[0..2], host memory) whose reconstruction
  * took its shortcut since timing was last enabled.  FP64: the global
- * indicator tau5 of eq. (25) is exactly zero, so every weight of eqs. (21)
- * and (28) is exactly d_k and the value is the linear combination of the
- * candidates of eq. (20) (bit-identical; no other indicator or division is
- * formed).  FP32 form: the stencil's spread is below 1e-30 and its centre
+ * indicator tau5 of eq. (25) is zero, or so small beside epsilon (below
+ * 2^-60 epsilon) that every weight of eqs. (21) and (28) rounds to d_k: the
+ * value is the linear combination of the candidates of eq. (20)
+ * (bit-identical; no other indicator or division is formed).  FP32 form: the stencil's spread is below 1e-30 and its centre
  * value is returned.  Counted by the stage sweeps of isweno_rhs and
  * isweno_rk3_step while timing is enabled (never inside a captured step).
  * Synchronises the device.  Errors: ISWENO_ERR_ARG for a null pointer,

@@ -49,11 +49,17 @@ __global__ __launch_bounds__(TL + 1) void batch_stage_kernel(BatchArgs g) {
   __shared__ T sq[NC * NP];
   __shared__ T sf[(NC + 1) * NF];
   __shared__ int s_status;
+  // a staged cell of the tile was not in_range: two flags in turn, the next
+  // tile's cleared while this one's is read
+  __shared__ int s_far[2];
   const int tid = threadIdx.x;
-  if (tid == 0) s_status = ST_OK;
+  if (tid == 0) {
+    s_status = ST_OK;
+    s_far[0] = 0;
+  }
   __syncthreads();
   const int64_t total = g.total;
-  int my3 = 0, my1 = 0;
+  int my3 = 0, my1 = 0, turn = 0;
   for (int64_t t = blockIdx.x; t < g.ntiles; t += gridDim.x) {
     const int prob = g.tprob[t];
     // problems that were non-physical when this step began are frozen (the
@@ -63,7 +69,7 @@ __global__ __launch_bounds__(TL + 1) void batch_stage_kernel(BatchArgs g) {
     const int64_t lo = g.offsets[prob], n = g.offsets[prob + 1] - lo;
     const int64_t l0 = g.tstart[t] - lo;
     const int len = (int)((n - l0) < TL ? (n - l0) : TL);
-    bool bad = false;
+    bool bad = false, far = false;
     // FP64: raised instruction priority while the tile is staged (its loads
     // go out ahead of the other workgroups' arithmetic), normal afterwards
     if constexpr (sizeof(T) == 8) __builtin_amdgcn_s_setprio(1);
@@ -72,9 +78,13 @@ __global__ __launch_bounds__(TL + 1) void batch_stage_kernel(BatchArgs g) {
       if (l >= n + 3) continue;
       bool flip;
       const int64_t li = bc_index(l, n, g.bc_lo, g.bc_hi, flip);
-      double q[NC];
-      cell_prim<1, T>(g.Uin, total, lo + li, q);
-      if (p >= 3 && p < 3 + len) bad = bad || !cell_ok<1>(g.Uin, total, lo + li, q);
+      double u[NC], q[NC];
+#pragma unroll
+      for (int c = 0; c < NC; c++) u[c] = g.Uin[c * total + lo + li];
+      cons_prim<1, T>(u, q);
+      const bool inr = in_range<1>(q);
+      far = far || !inr;
+      if (p >= 3 && p < 3 + len) bad = bad || !(inr ? c2_positive<1>(q) : cell_ok_u<1>(u, q));
       if (flip) q[1] = -q[1];
 #pragma unroll
       for (int c = 0; c < NC; c++) sq[c * NP + p] = T(q[c]);
@@ -83,15 +93,19 @@ __global__ __launch_bounds__(TL + 1) void batch_stage_kernel(BatchArgs g) {
       s_status = ST_NONPHYSICAL;
       atomicExch(&g.pstatus[prob], (int32_t)ST_NONPHYSICAL);
     }
+    if (far) s_far[turn] = 1;
     __syncthreads();
     if constexpr (sizeof(T) == 8) __builtin_amdgcn_s_setprio(0);
+    const TileState tile{!__builtin_amdgcn_readfirstlane(s_far[turn]) && eps_in_range(g.eps)};
+    turn ^= 1;
+    if (tid == 0) s_far[turn] = 0;
     for (int j = tid; j <= len; j += NTHR) {
       Lds1<T> st;
       st.base = &sq[j];
       st.cstride = NP;
       double F[NC], us;
       int n3, n1, nf;
-      face_flux<T, 1, 0, CUT>(st, kernel_weights<CUT>(g.weights), g.mood, g.eps, F, us, n3, n1,
+      face_flux<T, 1, 0, CUT>(st, tile, kernel_weights<CUT>(g.weights), g.mood, g.eps, F, us, n3, n1,
                               nf);
       if (j < len || l0 + j == n) {  // count each face of a problem once
         my3 += n3;

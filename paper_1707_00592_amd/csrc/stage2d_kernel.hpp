@@ -64,6 +64,7 @@ __global__ __launch_bounds__(kThreads, CUT && GATHER ? 2 : 4) void stage2d_kerne
   // are float values, so float storage is exact)
   __shared__ T sfy[(NC + 1) * NFY];
   __shared__ int s_status;
+  __shared__ int s_far;  // a staged cell was not in_range
   __shared__ int s_skip;
   // GATHER: faces whose MOOD check failed, per phase (face index | fail
   // bits << 16), redone by full waves after the phase's faces; the x faces
@@ -104,6 +105,7 @@ __global__ __launch_bounds__(kThreads, CUT && GATHER ? 2 : 4) void stage2d_kerne
       s_nq[1] = 0;
     }
     s_status = ST_OK;
+    s_far = 0;
     // sticky failure: one read per workgroup so that all lanes agree
     s_skip = g.stats ? (__atomic_load_n(&g.stats->status, __ATOMIC_RELAXED) != ST_OK) : 0;
   }
@@ -120,7 +122,7 @@ __global__ __launch_bounds__(kThreads, CUT && GATHER ? 2 : 4) void stage2d_kerne
   __builtin_amdgcn_s_setprio(1);
   // 1. stage primitives: the tile's interior cells, its rows extended by 3
   // cells each way along x and its columns by 3 each way along y
-  bool bad = false;
+  bool bad = false, far = false;
   double m = 0.0, h1 = 0.0;  // SPEEDS: the lane's max wave speed; FROM_L: dt
   if constexpr (FROM_L) h1 = *g.dt;
   const double dxs[2] = {g.dx[0], g.dx[1]};
@@ -144,8 +146,10 @@ __global__ __launch_bounds__(kThreads, CUT && GATHER ? 2 : 4) void stage2d_kerne
       else u[c] = g.Uin[c * N + cell];
     }
     cons_prim<NDIM, T>(u, q);
+    const bool inr = in_range<NDIM>(q);
+    far = far || !inr;
     if (colin && rowin) {
-      bad = bad || !cell_ok_u<NDIM>(u, q);
+      bad = bad || !(inr ? c2_positive<NDIM>(q) : cell_ok_u<NDIM>(u, q));
       if constexpr (SPEEDS) {
         const double sp = cell_speed<NDIM, T>(q, dxs);
         m = (sp > m || sp != sp) ? sp : m;
@@ -160,6 +164,7 @@ __global__ __launch_bounds__(kThreads, CUT && GATHER ? 2 : 4) void stage2d_kerne
   }
   if constexpr (SPEEDS) wave_max_bits(m, s_red);
   if (bad) s_status = ST_NONPHYSICAL;
+  if (far) s_far = 1;
   __syncthreads();
   __builtin_amdgcn_s_setprio(0);
   if (g.stats && tid == 0 && s_status != ST_OK) atomicExch(&g.stats->status, s_status);
@@ -173,6 +178,7 @@ __global__ __launch_bounds__(kThreads, CUT && GATHER ? 2 : 4) void stage2d_kerne
 
   int my3[2] = {0, 0}, my1[2] = {0, 0}, mys[2] = {0, 0};
   const int wts = kernel_weights<CUT>(g.weights);
+  const TileState tile{!__builtin_amdgcn_readfirstlane(s_far) && eps_in_range(g.eps)};
   const Div64<T> bydx(g.dx[0]), bydy(g.dx[1]);
   auto xstencil = [&](int f) {  // x face (f % 16, f / 16)
     LdsStencil2<T> st;
@@ -222,7 +228,7 @@ __global__ __launch_bounds__(kThreads, CUT && GATHER ? 2 : 4) void stage2d_kerne
       if (yvalid) {
         double G[NC], vs;
         int nsc;
-        fail = face_flux_first<T, NDIM, 1, CUT>(ystencil(tid), wts, g.eps, G, vs, nsc);
+        fail = face_flux_first<T, NDIM, 1, CUT>(ystencil(tid), tile, wts, g.eps, G, vs, nsc);
         if (ycounted(tid)) mys[1] += nsc;
         if (!fail) storey(tid, G, vs);
       }
@@ -244,7 +250,7 @@ __global__ __launch_bounds__(kThreads, CUT && GATHER ? 2 : 4) void stage2d_kerne
     } else if (yvalid) {
       double G[NC], vs;
       int n3, n1, nsc;
-      face_flux<T, NDIM, 1, CUT>(ystencil(tid), wts, g.mood, g.eps, G, vs, n3, n1, nsc);
+      face_flux<T, NDIM, 1, CUT>(ystencil(tid), tile, wts, g.mood, g.eps, G, vs, n3, n1, nsc);
       if (ycounted(tid)) {
         my3[1] += n3;
         my1[1] += n1;
@@ -269,7 +275,7 @@ __global__ __launch_bounds__(kThreads, CUT && GATHER ? 2 : 4) void stage2d_kerne
     int fail = 0;
     if (xvalid) {
       int nsc;
-      fail = face_flux_first<T, NDIM, 0, CUT>(xstencil(tid), wts, g.eps, F, us, nsc);
+      fail = face_flux_first<T, NDIM, 0, CUT>(xstencil(tid), tile, wts, g.eps, F, us, nsc);
       if (xcounted(tid)) mys[0] += nsc;
     }
     enqueue(0, tid, fail);
@@ -298,7 +304,7 @@ __global__ __launch_bounds__(kThreads, CUT && GATHER ? 2 : 4) void stage2d_kerne
     }
   } else if (xvalid) {
     int n3, n1, nsc;
-    face_flux<T, NDIM, 0, CUT>(xstencil(tid), wts, g.mood, g.eps, F, us, n3, n1, nsc);
+    face_flux<T, NDIM, 0, CUT>(xstencil(tid), tile, wts, g.mood, g.eps, F, us, n3, n1, nsc);
     if (xcounted(tid)) {
       my3[0] += n3;
       my1[0] += n1;

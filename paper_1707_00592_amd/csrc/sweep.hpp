@@ -195,6 +195,31 @@ __device__ __forceinline__ bool cell_ok_u(const double* u, const double* q) {
   return fin && admissible(q[0], q[1 + NDIM], q[2 + NDIM], q[3 + NDIM]);
 }
 
+// Whether a cell's primitives lie where the FP64 stage kernels may use the
+// unscaled divisions without a check per stencil (weno_f64_unit); every
+// finite state of ordinary materials does.  A cell in range is finite in
+// every component.
+template <int NDIM>
+__device__ __forceinline__ bool in_range(const double* q) {
+  bool ok = q[0] >= 0x1p-20 && q[0] <= 0x1p30 && fabs(q[1 + NDIM]) <= 0x1p40 &&
+            q[2 + NDIM] >= 0x1p-10 && q[2 + NDIM] <= 0x1p10 && fabs(q[3 + NDIM]) <= 0x1p40;
+#pragma unroll
+  for (int a = 0; a < NDIM; a++) ok = ok && fabs(q[1 + a]) <= 0x1p24;
+  return ok;
+}
+
+// The remaining condition of cell_ok for a cell in_range.
+template <int NDIM>
+__device__ __forceinline__ bool c2_positive(const double* q) {
+  return (q[2 + NDIM] + 1.0) * q[1 + NDIM] + q[3 + NDIM] > 0.0;
+}
+
+// What a workgroup knows of its whole staged tile when it starts on the
+// faces (the same for every lane).
+struct TileState {
+  bool fast;  // FP64: every staged cell in_range and epsilon too
+};
+
 // Face-order component k -> axis-order (LDS / conservative) component.
 template <int NDIM, int D>
 __device__ __host__ constexpr int axis_comp(int k) {
@@ -355,104 +380,64 @@ __device__ __forceinline__ void recon(const S& st, int sides, bool order3, int w
   }
 }
 
-// Full face: average state, eigen-parameters, both reconstructions, MOOD
-// cascade, HLLC.  F (face order) and us are written; o3/o1 report the
-// orders used (per side), nshort the field-sides of the first pass whose
-// reconstruction took its shortcut (weno<T>).
-// The weights a stage kernel evaluates: the cut-off form in the kernels
-// instantiated for it, else eq. (21) or eq. (28) as asked (those kernels
-// never see W_CUTOFF, and the compiler knows it).
-template <bool CUT>
-__device__ __forceinline__ int kernel_weights(int w) {
-  return CUT ? W_CUTOFF : (w == W_BASIC ? W_BASIC : W_MODIFIED);
+// The back-projection of field m's value r into a side's face-order state,
+// eq. (13), in field order.
+template <int NT>
+__device__ __forceinline__ void back_project(int m, double r, double bd, double gd, double* q) {
+  constexpr int NC = 5 + NT;
+  if (m == 0) {
+    q[0] = bd * r;
+    q[1] = (-gd) * r;
+    q[2 + NT] = r;
+  } else if (m == 1) {
+    q[0] = q[0] + r;
+  } else if (m == NC - 1) {
+    q[0] = q[0] + bd * r;
+    q[1] = q[1] + gd * r;
+    q[2 + NT] = q[2 + NT] + r;
+  } else {
+#pragma unroll
+    for (int t = 0; t < NT; t++)
+      if (m == 2 + t) q[2 + t] = r;
+    if (m == 2 + NT) q[3 + NT] = r;
+    if (m == 3 + NT) q[4 + NT] = r;
+  }
 }
 
-template <typename T, int NDIM, int D, bool CUT = false, class S>
-__device__ __forceinline__ void face_flux(const S& st, int weights, int mood,
-                                          double eps, double* F, double& us,
-                                          int& n3, int& n1, int& nshort,
-                                          MlpRun* mr = nullptr) {
+// 5th-order FP64 face states of a face in range, fully unrolled over the
+// fields as recon.
+template <int NDIM, int D, bool CUT, bool BASIC, class S>
+__device__ __forceinline__ void recon_fast(const S& st, double eps, double a, double b, double bd,
+                                           double gd, double* ql, double* qr, int& nshort) {
   constexpr int NT = NDIM - 1, NC = 5 + NT;
-  constexpr int CR = 0, CP = 1 + NDIM, CG = 2 + NDIM, CPI = 3 + NDIM;
-  // L_{i+1/2}: L of eq. (11) at the mean of the two primitive states.
-  const double rb = 0.5 * (st(CR, 2) + st(CR, 3));
-  const double pb = 0.5 * (st(CP, 2) + st(CP, 3));
-  const double Gb = 0.5 * (st(CG, 2) + st(CG, 3));
-  const double Pb = 0.5 * (st(CPI, 2) + st(CPI, 3));
-  T a, b;
-  double bd, gd;
-  {
-    const T c2 = sound2<T>(T(rb), T(pb), T(Gb), T(Pb));
-    const T c = sqrt(c2);
-    a = T(rb) * c / T(2);
-    b = qdiv<T>(T(1), c2);
-    bd = double(b);
-    gd = div64<T>(1.0, double(T(rb) * c));
-    if (sizeof(T) == 8) {
-      bd = 1.0 / double(c2);
+  constexpr int CR = 0, CU = 1 + D, CP = 1 + NDIM, CG = 2 + NDIM, CPI = 3 + NDIM;
+#pragma unroll
+  for (int m = 0; m < NC; m++) {
+    __builtin_amdgcn_sched_barrier(0);
+    double w[6];
+#pragma unroll
+    for (int j = 0; j < 6; j++) {
+      if (m == 0) w[j] = -a * st(CU, j) + 0.5 * st(CP, j);
+      else if (m == NC - 1) w[j] = a * st(CU, j) + 0.5 * st(CP, j);
+      else if (m == 1) w[j] = st(CR, j) - b * st(CP, j);
+      else if (m < 2 + NT) w[j] = st(1 + ((m - 2) < D ? (m - 2) : (m - 1)), j);
+      else w[j] = st(m == 2 + NT ? CG : CPI, j);
+    }
+#pragma unroll
+    for (int side = 0; side < 2; side++) {
+      __builtin_amdgcn_sched_barrier(0);
+      const double v0 = side ? w[5] : w[0], v1 = side ? w[4] : w[1], v2 = side ? w[3] : w[2],
+                   v3 = side ? w[2] : w[3], v4 = side ? w[1] : w[4];
+      double r;
+      if constexpr (CUT) r = weno_f64_cutoff_unit(v0, v1, v2, v3, v4, eps, nshort);
+      else r = weno_f64_unit<BASIC>(v0, v1, v2, v3, v4, eps, nshort);
+      back_project<NT>(m, r, bd, gd, side ? qr : ql);
     }
   }
-  double ql[NC], qr[NC];
-  if (mr) mlp_material(Gb, Pb, mr->f6, mr->f7);
-  nshort = 0;
-  recon<T, NDIM, D, CUT>(st, 3, false, weights, T(eps), a, b, bd, gd, ql, qr, nshort, mr);
-  n3 = 0;
-  n1 = 0;
-  if (mood) {
-    // Sec. 3.4: redo a failing side without the 3-point stencils, then fall
-    // back to the first-order state of eq. (32) (the cell's own primitive
-    // state, since R L q_i = q_i).
-    int fail = (admissible(ql[0], ql[2 + NT], ql[3 + NT], ql[4 + NT]) ? 0 : 1) |
-               (admissible(qr[0], qr[2 + NT], qr[3 + NT], qr[4 + NT]) ? 0 : 2);
-    if (mr && fail) {
-      // learned weights: a failing side is first redone with the plain
-      // 5th-order WENO-IS weights of eq. (28) (counted as a fallback of the
-      // network); the cascade below then starts from that state
-      int nfl = 0;
-      recon<T, NDIM, D>(st, fail, false, W_MODIFIED, T(eps), a, b, bd, gd, ql, qr, nfl);
-      mr->fallbacks += (fail & 1) + (fail >> 1);
-      fail = (admissible(ql[0], ql[2 + NT], ql[3 + NT], ql[4 + NT]) ? 0 : 1) |
-             (admissible(qr[0], qr[2 + NT], qr[3 + NT], qr[4 + NT]) ? 0 : 2);
-    }
-    if (fail) {
-      int nf3 = 0;
-      recon<T, NDIM, D, CUT>(st, fail, true, weights, T(eps), a, b, bd, gd, ql, qr, nf3);
-#pragma unroll
-      for (int side = 0; side < 2; side++) {
-        if (!(fail & (1 << side))) continue;
-        double* q = side ? qr : ql;
-        // counted without a branch: a counter picked by a branch ends up
-        // in private (scratch) memory on every face
-        const int ok = admissible(q[0], q[2 + NT], q[3 + NT], q[4 + NT]) ? 1 : 0;
-        if (!ok) {
-          const int j = side ? 3 : 2;
-#pragma unroll
-          for (int k = 0; k < NC; k++) q[k] = st(axis_comp<NDIM, D>(k), j);
-        }
-        n3 += ok;
-        n1 += 1 - ok;
-      }
-    }
-  }
-  T tl[NC], tr[NC], tF[NC], tus;
-#pragma unroll
-  for (int k = 0; k < NC; k++) {
-    tl[k] = T(ql[k]);
-    tr[k] = T(qr[k]);
-  }
-  hllc<T, NT>(tl, tr, tF, tus);
-#pragma unroll
-  for (int k = 0; k < NC; k++) F[k] = double(tF[k]);
-  us = double(tus);
 }
 
-// The same face in two passes, for a kernel that gathers the faces the
-// MOOD cascade needs and redoes them by full waves.  First pass: the
-// 5th-order states and their check; a face with a failing side returns its
-// fail bits (non-zero) and no flux.  Second pass (face_flux_redo, on the
-// gathered faces): the 5th-order states are formed again (the same bits),
-// the failing sides go through the cascade, then HLLC -- the flux that
-// face_flux gives, bit for bit.
+// L_{i+1/2}: L of eq. (11) at the mean of the two primitive states, as the
+// parameters a = rho c / 2, b = 1/c^2 and, in FP64, bd = b, gd = 1/(rho c).
 template <typename T, int NDIM, class S>
 __device__ __forceinline__ void face_params(const S& st, T& a, T& b, double& bd, double& gd) {
   constexpr int CR = 0, CP = 1 + NDIM, CG = 2 + NDIM, CPI = 3 + NDIM;
@@ -471,49 +456,34 @@ __device__ __forceinline__ void face_params(const S& st, T& a, T& b, double& bd,
   }
 }
 
-template <typename T, int NDIM, int D, bool CUT = false, class S>
-__device__ __forceinline__ int face_flux_first(const S& st, int weights, double eps, double* F,
-                                               double& us, int& nshort) {
-  constexpr int NT = NDIM - 1, NC = 5 + NT;
-  T a, b;
-  double bd, gd;
-  face_params<T, NDIM>(st, a, b, bd, gd);
-  double ql[NC], qr[NC];
-  nshort = 0;
-  recon<T, NDIM, D, CUT>(st, 3, false, weights, T(eps), a, b, bd, gd, ql, qr, nshort);
-  const int fail = (admissible(ql[0], ql[2 + NT], ql[3 + NT], ql[4 + NT]) ? 0 : 1) |
-                   (admissible(qr[0], qr[2 + NT], qr[3 + NT], qr[4 + NT]) ? 0 : 2);
-  if (fail) return fail;
-  T tl[NC], tr[NC], tF[NC], tus;
-#pragma unroll
-  for (int k = 0; k < NC; k++) {
-    tl[k] = T(ql[k]);
-    tr[k] = T(qr[k]);
-  }
-  hllc<T, NT>(tl, tr, tF, tus);
-#pragma unroll
-  for (int k = 0; k < NC; k++) F[k] = double(tF[k]);
-  us = double(tus);
-  return 0;
+// The weights a stage kernel evaluates: the cut-off form in the kernels
+// instantiated for it, else eq. (21) or eq. (28) as asked (those kernels
+// never see W_CUTOFF, and the compiler knows it).
+template <bool CUT>
+__device__ __forceinline__ int kernel_weights(int w) {
+  return CUT ? W_CUTOFF : (w == W_BASIC ? W_BASIC : W_MODIFIED);
 }
 
-template <typename T, int NDIM, int D, bool CUT = false, class S>
-__device__ __forceinline__ void face_flux_redo(const S& st, int fail, int weights, double eps,
-                                               double* F, double& us, int& n3, int& n1) {
+// The fail bits of a face's two states (bit 0 left, bit 1 right), Sec. 3.4.
+template <int NT>
+__device__ __forceinline__ int mood_fail(const double* ql, const double* qr) {
+  return (admissible(ql[0], ql[2 + NT], ql[3 + NT], ql[4 + NT]) ? 0 : 1) |
+         (admissible(qr[0], qr[2 + NT], qr[3 + NT], qr[4 + NT]) ? 0 : 2);
+}
+
+// The end of the cascade: a failing side whose 3rd-order state fails too
+// takes the first-order state of eq. (32) (the cell's own primitive state,
+// since R L q_i = q_i).
+template <int NDIM, int D, class S>
+__device__ __forceinline__ void first_order(const S& st, int fail, double* ql, double* qr, int& n3,
+                                            int& n1) {
   constexpr int NT = NDIM - 1, NC = 5 + NT;
-  T a, b;
-  double bd, gd;
-  face_params<T, NDIM>(st, a, b, bd, gd);
-  double ql[NC], qr[NC];
-  int nsc = 0, nf3 = 0;
-  recon<T, NDIM, D, CUT>(st, 3, false, weights, T(eps), a, b, bd, gd, ql, qr, nsc);
-  recon<T, NDIM, D, CUT>(st, fail, true, weights, T(eps), a, b, bd, gd, ql, qr, nf3);
-  n3 = 0;
-  n1 = 0;
 #pragma unroll
   for (int side = 0; side < 2; side++) {
     if (!(fail & (1 << side))) continue;
     double* q = side ? qr : ql;
+    // counted without a branch: a counter picked by a branch ends up
+    // in private (scratch) memory on every face
     const int ok = admissible(q[0], q[2 + NT], q[3 + NT], q[4 + NT]) ? 1 : 0;
     if (!ok) {
       const int j = side ? 3 : 2;
@@ -523,6 +493,12 @@ __device__ __forceinline__ void face_flux_redo(const S& st, int fail, int weight
     n3 += ok;
     n1 += 1 - ok;
   }
+}
+
+template <typename T, int NT>
+__device__ __forceinline__ void states_flux(const double* ql, const double* qr, double* F,
+                                            double& us) {
+  constexpr int NC = 5 + NT;
   T tl[NC], tr[NC], tF[NC], tus;
 #pragma unroll
   for (int k = 0; k < NC; k++) {
@@ -533,6 +509,157 @@ __device__ __forceinline__ void face_flux_redo(const S& st, int fail, int weight
 #pragma unroll
   for (int k = 0; k < NC; k++) F[k] = double(tF[k]);
   us = double(tus);
+}
+
+// An FP64 face of a tile in range, 5th order and no cascade.  Returns true
+// when that is not the face's flux: a sound speed outside the range of the
+// unscaled divisions or (mood) a state that fails the positivity check; it
+// is then evaluated by face_general.  The two share no value: with the
+// general reconstruction and the cascade behind a branch inside this path the
+// 2D stage took 5-8% longer on states that never reach them.
+template <int NDIM, int D, bool CUT, class S>
+__device__ __forceinline__ bool face_common(const S& st, int weights, int mood, double eps,
+                                            double* F, double& us, int& nshort) {
+  constexpr int NT = NDIM - 1, NC = 5 + NT;
+  double a, b, bd, gd, ql[NC], qr[NC];
+  face_params<double, NDIM>(st, a, b, bd, gd);
+  nshort = 0;
+  // b = 1/c^2 of the mean state: c^2 >= kFaceC2Min
+  bool bad = !(b > 0.0 && b <= 1.0 / kFaceC2Min);
+  if (!CUT && weights == W_BASIC)
+    recon_fast<NDIM, D, CUT, true>(st, eps, a, b, bd, gd, ql, qr, nshort);
+  else
+    recon_fast<NDIM, D, CUT, false>(st, eps, a, b, bd, gd, ql, qr, nshort);
+  bad = bad || (mood && mood_fail<NT>(ql, qr));
+  states_flux<double, NT>(ql, qr, F, us);
+  return bad;
+}
+
+// An FP64 face in general: any range, with the cascade.
+template <int NDIM, int D, bool CUT, class S>
+__device__ __forceinline__ void face_general(const S& st, int weights, int mood, double eps,
+                                             double* F, double& us, int& n3, int& n1,
+                                             int& nshort) {
+  constexpr int NT = NDIM - 1, NC = 5 + NT;
+  double a, b, bd, gd, ql[NC], qr[NC];
+  face_params<double, NDIM>(st, a, b, bd, gd);
+  nshort = 0;
+  recon<double, NDIM, D, CUT>(st, 3, false, weights, eps, a, b, bd, gd, ql, qr, nshort);
+  n3 = 0;
+  n1 = 0;
+  if (mood) {
+    const int fail = mood_fail<NT>(ql, qr);
+    if (fail) {
+      int n = 0;
+      recon<double, NDIM, D, CUT>(st, fail, true, weights, eps, a, b, bd, gd, ql, qr, n);
+      first_order<NDIM, D>(st, fail, ql, qr, n3, n1);
+    }
+  }
+  states_flux<double, NT>(ql, qr, F, us);
+}
+
+// Full face: average state, eigen-parameters, both reconstructions, MOOD
+// cascade, HLLC.  F (face order) and us are written; n3/n1 report the
+// orders used (per side), nshort the field-sides of the first pass whose
+// reconstruction took its shortcut.  FP64: a wave with a face that is not
+// face_common's evaluates all its faces by face_general (the same bits).
+template <typename T, int NDIM, int D, bool CUT = false, class S>
+__device__ __forceinline__ void face_flux(const S& st, const TileState& tile, int weights,
+                                          int mood, double eps, double* F, double& us,
+                                          int& n3, int& n1, int& nshort,
+                                          MlpRun* mr = nullptr) {
+  constexpr int NT = NDIM - 1, NC = 5 + NT;
+  if constexpr (sizeof(T) == 8) {
+    bool other = true;
+    n3 = 0;
+    n1 = 0;
+    if (tile.fast) other = face_common<NDIM, D, CUT>(st, weights, mood, eps, F, us, nshort);
+    if (__any(other)) face_general<NDIM, D, CUT>(st, weights, mood, eps, F, us, n3, n1, nshort);
+    return;
+  } else {
+  T a, b;
+  double bd, gd, ql[NC], qr[NC];
+  face_params<T, NDIM>(st, a, b, bd, gd);
+  if (mr) {
+    constexpr int CG = 2 + NDIM, CPI = 3 + NDIM;
+    const double Gb = 0.5 * (st(CG, 2) + st(CG, 3));
+    const double Pb = 0.5 * (st(CPI, 2) + st(CPI, 3));
+    mlp_material(Gb, Pb, mr->f6, mr->f7);
+  }
+  nshort = 0;
+  recon<T, NDIM, D, CUT>(st, 3, false, weights, T(eps), a, b, bd, gd, ql, qr, nshort, mr);
+  n3 = 0;
+  n1 = 0;
+  if (mood) {
+    // Sec. 3.4: redo a failing side without the 3-point stencils, then fall
+    // back to the first-order state
+    int fail = mood_fail<NT>(ql, qr);
+    if (mr && fail) {
+      // learned weights: a failing side is first redone with the plain
+      // 5th-order WENO-IS weights of eq. (28) (counted as a fallback of the
+      // network); the cascade below then starts from that state
+      int nfl = 0;
+      recon<T, NDIM, D>(st, fail, false, W_MODIFIED, T(eps), a, b, bd, gd, ql, qr, nfl);
+      mr->fallbacks += (fail & 1) + (fail >> 1);
+      fail = mood_fail<NT>(ql, qr);
+    }
+    if (fail) {
+      int nf3 = 0;
+      recon<T, NDIM, D, CUT>(st, fail, true, weights, T(eps), a, b, bd, gd, ql, qr, nf3);
+      first_order<NDIM, D>(st, fail, ql, qr, n3, n1);
+    }
+  }
+  states_flux<T, NT>(ql, qr, F, us);
+  }
+}
+
+// The same face in two passes, for a kernel that gathers the faces the
+// MOOD cascade needs and redoes them by full waves.  First pass: the
+// 5th-order states and their check; a face with a failing side returns its
+// fail bits (non-zero) and no flux.  Second pass (face_flux_redo, on the
+// gathered faces): the whole face again with the cascade -- the flux that
+// face_flux gives, bit for bit.  FP64: a face face_common does not evaluate
+// is gathered as well, and the second pass is face_general.
+template <typename T, int NDIM, int D, bool CUT = false, class S>
+__device__ __forceinline__ int face_flux_first(const S& st, const TileState& tile, int weights,
+                                               double eps, double* F, double& us, int& nshort) {
+  constexpr int NT = NDIM - 1, NC = 5 + NT;
+  nshort = 0;
+  if constexpr (sizeof(T) == 8) {
+    if (!tile.fast) return 1;
+    return face_common<NDIM, D, CUT>(st, weights, 1, eps, F, us, nshort) ? 1 : 0;
+  } else {
+    T a, b;
+    double bd, gd, ql[NC], qr[NC];
+    face_params<T, NDIM>(st, a, b, bd, gd);
+    recon<T, NDIM, D, CUT>(st, 3, false, weights, T(eps), a, b, bd, gd, ql, qr, nshort);
+    const int fail = mood_fail<NT>(ql, qr);
+    if (!fail) states_flux<T, NT>(ql, qr, F, us);
+    return fail;
+  }
+}
+
+// fail: face_flux_first's; nshort the first pass's count, replaced where
+// this pass forms the first one's states anew.
+template <typename T, int NDIM, int D, bool CUT = false, class S>
+__device__ __forceinline__ void face_flux_redo(const S& st, int fail, int weights, double eps,
+                                               double* F, double& us, int& n3, int& n1) {
+  constexpr int NT = NDIM - 1, NC = 5 + NT;
+  if constexpr (sizeof(T) == 8) {
+    int nsc;
+    face_general<NDIM, D, CUT>(st, weights, 1, eps, F, us, n3, n1, nsc);
+  } else {
+    T a, b;
+    double bd, gd, ql[NC], qr[NC];
+    face_params<T, NDIM>(st, a, b, bd, gd);
+    int nsc = 0, nf3 = 0;
+    recon<T, NDIM, D, CUT>(st, 3, false, weights, T(eps), a, b, bd, gd, ql, qr, nsc);
+    recon<T, NDIM, D, CUT>(st, fail, true, weights, T(eps), a, b, bd, gd, ql, qr, nf3);
+    n3 = 0;
+    n1 = 0;
+    first_order<NDIM, D>(st, fail, ql, qr, n3, n1);
+    states_flux<T, NT>(ql, qr, F, us);
+  }
 }
 
 }  // namespace isw

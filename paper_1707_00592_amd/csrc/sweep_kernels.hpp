@@ -101,6 +101,7 @@ __global__ __launch_bounds__(NTHR, MODE == OUT_PARTIAL_S ? 5 : 1) void sweep_ker
   T* const sq = reinterpret_cast<T*>(lds);
   T* const sf = reinterpret_cast<T*>(lds + SF_OFF);
   __shared__ int s_status;
+  __shared__ int s_far;  // a staged cell was not in_range
   __shared__ int s_skip;
   // OUT_PARTIAL_S: this x sweep also finds its tile's max wave speed (the
   // step's time step; the tiles of an x sweep hold every cell once)
@@ -120,6 +121,7 @@ __global__ __launch_bounds__(NTHR, MODE == OUT_PARTIAL_S ? 5 : 1) void sweep_ker
   const int tid = threadIdx.x;
   if (tid == 0) {
     s_status = ST_OK;
+    s_far = 0;
     // sticky failure: one read per workgroup so that all lanes agree
     s_skip = g.stats ? (__atomic_load_n(&g.stats->status, __ATOMIC_RELAXED) != ST_OK) : 0;
   }
@@ -142,7 +144,7 @@ __global__ __launch_bounds__(NTHR, MODE == OUT_PARTIAL_S ? 5 : 1) void sweep_ker
   // (the float sweeps ran slower with it)
   if constexpr (sizeof(T) == 8) __builtin_amdgcn_s_setprio(1);
   // 1. stage primitives (FP64) with ghost cells
-  bool bad = false;
+  bool bad = false, far = false;
   double m = 0.0;  // SPEEDS: the lane's max wave speed
   const double dxs[3] = {g.dx[0], g.dx[1], g.dx[2]};
   for (int e = tid; e < TW * NP; e += NTHR) {
@@ -154,10 +156,14 @@ __global__ __launch_bounds__(NTHR, MODE == OUT_PARTIAL_S ? 5 : 1) void sweep_ker
     bool flip;
     const int64_t li = bc_index(l, geo.nL, g.bc_lo, g.bc_hi, flip);
     const int64_t cell = a * geo.sA + li * geo.sL + tt * geo.sT;
-    double q[NC];
-    cell_prim<NDIM, T>(g.Uin, N, cell, q);
+    double u[NC], q[NC];
+#pragma unroll
+    for (int c = 0; c < NC; c++) u[c] = g.Uin[c * N + cell];
+    cons_prim<NDIM, T>(u, q);
+    const bool inr = in_range<NDIM>(q);
+    far = far || !inr;
     if (p >= 3 && p < 3 + TL && l < geo.nL) {
-      bad = bad || !cell_ok<NDIM>(g.Uin, N, cell, q);
+      bad = bad || !(inr ? c2_positive<NDIM>(q) : cell_ok_u<NDIM>(u, q));
       if constexpr (SPEEDS) {
         const double sp = cell_speed<NDIM, T>(q, dxs);
         m = (sp > m || sp != sp) ? sp : m;
@@ -169,6 +175,7 @@ __global__ __launch_bounds__(NTHR, MODE == OUT_PARTIAL_S ? 5 : 1) void sweep_ker
   }
   if constexpr (SPEEDS) wave_max_bits(m, s_red);
   if (bad) s_status = ST_NONPHYSICAL;
+  if (far) s_far = 1;
   __syncthreads();
   if constexpr (sizeof(T) == 8) __builtin_amdgcn_s_setprio(0);
   if constexpr (SPEEDS) {
@@ -181,6 +188,7 @@ __global__ __launch_bounds__(NTHR, MODE == OUT_PARTIAL_S ? 5 : 1) void sweep_ker
 
   // 2. faces: thread tid owns face (w, j); with ALIAS the values wait in
   // registers until every face has read sq
+  const TileState tile{!__builtin_amdgcn_readfirstlane(s_far) && eps_in_range(g.eps)};
   int my3 = 0, my1 = 0, mys = 0;
   // FP64 x tiles of 8 rows x 32 faces: each wave takes an 8 x 8 block, so a
   // front across x splits fewer waves between the linear-weight form and
@@ -198,7 +206,7 @@ __global__ __launch_bounds__(NTHR, MODE == OUT_PARTIAL_S ? 5 : 1) void sweep_ker
     st.cstride = D == 0 ? TW * NP : NP * TW;
     st.pstride = D == 0 ? 1 : TW;
     int n3, n1, nf;
-    face_flux<T, NDIM, D, CUT>(st, kernel_weights<CUT>(g.weights), g.mood, g.eps, F, us, n3, n1,
+    face_flux<T, NDIM, D, CUT>(st, tile, kernel_weights<CUT>(g.weights), g.mood, g.eps, F, us, n3, n1,
                           nf);
     // the face on a tile boundary is evaluated by both tiles; count it once
     // (in the tile to its right, or the last tile for the domain's last face)
@@ -371,7 +379,7 @@ __global__ __launch_bounds__(NTHR) void sweep_mlp_kernel(SweepArgs g) {
     st.pstride = D == 0 ? 1 : TW;
     double F[NC], us;
     int n3, n1, nf;
-    face_flux<T, NDIM, D>(st, g.weights, g.mood, g.eps, F, us, n3, n1, nf, &mr);
+    face_flux<T, NDIM, D>(st, TileState{false}, g.weights, g.mood, g.eps, F, us, n3, n1, nf, &mr);
     if (!valid) continue;
     // the face on a tile boundary is evaluated by both tiles; count it once
     // (in the tile to its right, or the last tile for the domain's last face)
