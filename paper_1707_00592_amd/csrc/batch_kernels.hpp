@@ -42,24 +42,17 @@ struct Lds1 {
 };
 
 template <typename T, int TL, int MODE, bool CUT>
-__global__ __launch_bounds__(TL + 1) void batch_stage_kernel(BatchArgs g) {
+__global__ __launch_bounds__(TL + 1, sizeof(T) == 4 ? 6 : 1) void batch_stage_kernel(BatchArgs g) {
   constexpr int NC = 5, NP = TL + 6, NF = TL + 1, NTHR = TL + 1;
   // FP64 primitives and the face values, both in the arithmetic's type (the
   // float form reconstructs from float values and its fluxes are float)
   __shared__ T sq[NC * NP];
   __shared__ T sf[(NC + 1) * NF];
-  __shared__ int s_status;
-  // a staged cell of the tile was not in_range: two flags in turn, the next
-  // tile's cleared while this one's is read
-  __shared__ int s_far[2];
+  __shared__ TileNotes<NTHR / 64> s_notes;
   const int tid = threadIdx.x;
-  if (tid == 0) {
-    s_status = ST_OK;
-    s_far[0] = 0;
-  }
-  __syncthreads();
+  int failed = 0;  // a cell of any of this workgroup's tiles was non-physical
   const int64_t total = g.total;
-  int my3 = 0, my1 = 0, turn = 0;
+  int my3 = 0, my1 = 0;
   for (int64_t t = blockIdx.x; t < g.ntiles; t += gridDim.x) {
     const int prob = g.tprob[t];
     // problems that were non-physical when this step began are frozen (the
@@ -69,7 +62,10 @@ __global__ __launch_bounds__(TL + 1) void batch_stage_kernel(BatchArgs g) {
     const int64_t lo = g.offsets[prob], n = g.offsets[prob + 1] - lo;
     const int64_t l0 = g.tstart[t] - lo;
     const int len = (int)((n - l0) < TL ? (n - l0) : TL);
-    bool bad = false, far = false;
+    int found = 0;
+    double ref[NC];  // the tile's first cell
+#pragma unroll
+    for (int c = 0; c < NC; c++) ref[c] = g.Uin[c * total + lo + l0];
     // FP64: raised instruction priority while the tile is staged (its loads
     // go out ahead of the other workgroups' arithmetic), normal afterwards
     if constexpr (sizeof(T) == 8) __builtin_amdgcn_s_setprio(1);
@@ -81,24 +77,48 @@ __global__ __launch_bounds__(TL + 1) void batch_stage_kernel(BatchArgs g) {
       double u[NC], q[NC];
 #pragma unroll
       for (int c = 0; c < NC; c++) u[c] = g.Uin[c * total + lo + li];
+      found |= differs<NC>(u, ref, flip) ? TILE_MIXED : 0;
       cons_prim<1, T>(u, q);
-      const bool inr = in_range<1>(q);
-      far = far || !inr;
-      if (p >= 3 && p < 3 + len) bad = bad || !(inr ? c2_positive<1>(q) : cell_ok_u<1>(u, q));
+      const bool inr = sizeof(T) == 8 && in_range<1>(q);
+      if constexpr (sizeof(T) == 8) found |= inr ? 0 : TILE_FAR;
+      if (p >= 3 && p < 3 + len) found |= (inr ? c2_positive<1>(q) : cell_ok_u<1>(u, q)) ? 0 : TILE_BAD;
       if (flip) q[1] = -q[1];
 #pragma unroll
       for (int c = 0; c < NC; c++) sq[c * NP + p] = T(q[c]);
     }
-    if (bad) {
-      s_status = ST_NONPHYSICAL;
-      atomicExch(&g.pstatus[prob], (int32_t)ST_NONPHYSICAL);
-    }
-    if (far) s_far[turn] = 1;
+    if (found & TILE_BAD) atomicExch(&g.pstatus[prob], (int32_t)ST_NONPHYSICAL);
+    s_notes.note(found);
     __syncthreads();
     if constexpr (sizeof(T) == 8) __builtin_amdgcn_s_setprio(0);
-    const TileState tile{!__builtin_amdgcn_readfirstlane(s_far[turn]) && eps_in_range(g.eps)};
-    turn ^= 1;
-    if (tid == 0) s_far[turn] = 0;
+    const int notes = s_notes.all();
+    failed |= notes & TILE_BAD;
+    const TileState tile{!(notes & TILE_FAR) && eps_in_range(g.eps)};
+    const double h = g.dt[prob];
+    // the output step of a cell's component (offset o) from its L and the
+    // stage input there
+    auto put = [&](int64_t o, double L, auto uin) {
+      if (MODE == OUT_RK1) {
+        g.Uout[o] = g.U0[o] + h * L;
+      } else if (MODE == OUT_RK2) {
+        g.Uout[o] = 0.75 * g.U0[o] + 0.25 * (uin(o) + h * L);
+      } else {
+        g.Uout[o] = (1.0 / 3.0) * g.U0[o] + (2.0 / 3.0) * (uin(o) + h * L);
+      }
+    };
+    // a uniform tile (steady_state): every face has the same flux
+    if (!(notes & TILE_MIXED)) {
+      double q[NC];
+      cons_prim<1, T>(ref, q);
+      if (steady_state<1>(q)) {
+        for (int j = tid; j < len; j += NTHR)
+#pragma unroll
+          for (int c = 0; c < NC; c++)
+            put(c * total + lo + l0 + j, steady_term(c >= 3, q[c]),
+                [&](int64_t) { return ref[c]; });
+        __syncthreads();  // the notes are reused by the next tile
+        continue;
+      }
+    }
     for (int j = tid; j <= len; j += NTHR) {
       Lds1<T> st;
       st.base = &sq[j];
@@ -117,7 +137,6 @@ __global__ __launch_bounds__(TL + 1) void batch_stage_kernel(BatchArgs g) {
     }
     __syncthreads();
     const Div64<T> bydx(g.dx[prob]);
-    const double h = g.dt[prob];
     for (int j = tid; j < len; j += NTHR) {
       const int64_t cell = lo + l0 + j;
 #pragma unroll
@@ -126,14 +145,7 @@ __global__ __launch_bounds__(TL + 1) void batch_stage_kernel(BatchArgs g) {
         if (k >= 3)
           r = r + bydx(double(sq[k * NP + j + 3]) *
                        (double(sf[NC * NF + j + 1]) - double(sf[NC * NF + j])));
-        const int64_t o = k * total + cell;
-        if (MODE == OUT_RK1) {
-          g.Uout[o] = g.U0[o] + h * r;
-        } else if (MODE == OUT_RK2) {
-          g.Uout[o] = 0.75 * g.U0[o] + 0.25 * (g.Uin[o] + h * r);
-        } else {
-          g.Uout[o] = (1.0 / 3.0) * g.U0[o] + (2.0 / 3.0) * (g.Uin[o] + h * r);
-        }
+        put(k * total + cell, r, [&](int64_t o) { return g.Uin[o]; });
       }
     }
     __syncthreads();  // LDS is reused by the next tile
@@ -141,7 +153,7 @@ __global__ __launch_bounds__(TL + 1) void batch_stage_kernel(BatchArgs g) {
   if (g.stats) {
     if (my3) atomicAdd(&g.stats->o3[0], (unsigned long long)my3);
     if (my1) atomicAdd(&g.stats->o1[0], (unsigned long long)my1);
-    if (tid == 0 && s_status != ST_OK) atomicExch(&g.stats->status, s_status);
+    if (tid == 0 && failed) atomicExch(&g.stats->status, (int)ST_NONPHYSICAL);
   }
 }
 

@@ -63,9 +63,7 @@ __global__ __launch_bounds__(kThreads, CUT && GATHER ? 2 : 4) void stage2d_kerne
   // y-face fluxes and v* in the arithmetic's type (the float form's fluxes
   // are float values, so float storage is exact)
   __shared__ T sfy[(NC + 1) * NFY];
-  __shared__ int s_status;
-  __shared__ int s_far;  // a staged cell was not in_range
-  __shared__ int s_skip;
+  __shared__ TileNotes<NTHR / 64> s_notes;
   // GATHER: faces whose MOOD check failed, per phase (face index | fail
   // bits << 16), redone by full waves after the phase's faces; the x faces
   // redone hand their values back through sfx
@@ -84,35 +82,29 @@ __global__ __launch_bounds__(kThreads, CUT && GATHER ? 2 : 4) void stage2d_kerne
   // along tile rows (x-neighbours, whose halo lines overlap, share an L2)
   // and visits the rows as 0, 8, 16, ..., 1, 9, ... (every XCD gets rows
   // spread over the whole height, so fronts stay evenly shared).
-  const int64_t ntx = (nx + TX - 1) / TX, nty = (ny + TY - 1) / TY;
-  const int64_t ntiles = ntx * nty;
-  const int64_t xcd = blockIdx.x & 7, k = blockIdx.x >> 3;
-  const int64_t per = ntiles >> 3, extra = ntiles & 7;
-  const int64_t pos = xcd * per + (xcd < extra ? xcd : extra) + k;
-  const int64_t prow = pos / ntx;
-  int64_t cls = 0, first = 0;  // rows cls, cls + 8, ... hold positions first ...
+  // (tile numbers fit 31 bits, as the launch does)
+  const unsigned ntx = (unsigned)((nx + TX - 1) / TX), nty = (unsigned)((ny + TY - 1) / TY);
+  const unsigned ntiles = ntx * nty;
+  const unsigned xcd = blockIdx.x & 7, k = blockIdx.x >> 3;
+  const unsigned per = ntiles >> 3, extra = ntiles & 7;
+  const unsigned pos = xcd * per + (xcd < extra ? xcd : extra) + k;
+  const unsigned prow = pos / ntx;
+  unsigned cls = 0, first = 0;  // rows cls, cls + 8, ... hold positions first ...
   while (prow >= first + ((nty - cls + 7) >> 3)) {
     first += (nty - cls + 7) >> 3;
     cls++;
   }
-  const int64_t gx0 = (pos % ntx) * TX;
-  const int64_t gy0 = (cls + 8 * (prow - first)) * TY;
+  const int64_t gx0 = (int64_t)(pos - prow * ntx) * TX;
+  const int64_t gy0 = (int64_t)(cls + 8 * (prow - first)) * TY;
   const int tid = threadIdx.x;
 
+  bool skip = false;
   if (tid == 0) {
     if constexpr (GATHER) {
       s_nq[0] = 0;
       s_nq[1] = 0;
     }
-    s_status = ST_OK;
-    s_far = 0;
-    // sticky failure: one read per workgroup so that all lanes agree
-    s_skip = g.stats ? (__atomic_load_n(&g.stats->status, __ATOMIC_RELAXED) != ST_OK) : 0;
-  }
-  __syncthreads();
-  if (s_skip) {
-    if (SPEEDS && tid == 0) g.cflp[blockIdx.x] = 0ull;
-    return;
+    skip = latched(g.stats);
   }
 
   // The waves of a workgroup that is staging its tile run at a raised
@@ -122,10 +114,20 @@ __global__ __launch_bounds__(kThreads, CUT && GATHER ? 2 : 4) void stage2d_kerne
   __builtin_amdgcn_s_setprio(1);
   // 1. stage primitives: the tile's interior cells, its rows extended by 3
   // cells each way along x and its columns by 3 each way along y
-  bool bad = false, far = false;
+  int found = skip ? TILE_SKIP : 0;
   double m = 0.0, h1 = 0.0;  // SPEEDS: the lane's max wave speed; FROM_L: dt
   if constexpr (FROM_L) h1 = *g.dt;
   const double dxs[2] = {g.dx[0], g.dx[1]};
+  // the stage input at a cell
+  auto input = [&](int64_t cell, double* u) {
+#pragma unroll
+    for (int c = 0; c < NC; c++) {
+      if constexpr (FROM_L) u[c] = g.U0[c * N + cell] + h1 * g.R[c * N + cell];
+      else u[c] = g.Uin[c * N + cell];
+    }
+  };
+  double ref[NC];
+  input(gy0 * nx + gx0, ref);
   for (int e = tid; e < QROW; e += NTHR) {
     const int yy = e / SX, xx = e % SX;
     const int64_t gxl = gx0 + xx - 3, gyl = gy0 + yy - 3;
@@ -140,16 +142,13 @@ __global__ __launch_bounds__(kThreads, CUT && GATHER ? 2 : 4) void stage2d_kerne
     if (yhalo) iy = bc_index(gyl, ny, g.bcl[1], g.bch[1], flip);
     const int64_t cell = iy * nx + ix;
     double u[NC], q[NC];
-#pragma unroll
-    for (int c = 0; c < NC; c++) {
-      if constexpr (FROM_L) u[c] = g.U0[c * N + cell] + h1 * g.R[c * N + cell];
-      else u[c] = g.Uin[c * N + cell];
-    }
+    input(cell, u);
+    found |= differs<NC>(u, ref, flip) ? TILE_MIXED : 0;
     cons_prim<NDIM, T>(u, q);
-    const bool inr = in_range<NDIM>(q);
-    far = far || !inr;
+    const bool inr = sizeof(T) == 8 && in_range<NDIM>(q);
+    if constexpr (sizeof(T) == 8) found |= inr ? 0 : TILE_FAR;
     if (colin && rowin) {
-      bad = bad || !(inr ? c2_positive<NDIM>(q) : cell_ok_u<NDIM>(u, q));
+      found |= (inr ? c2_positive<NDIM>(q) : cell_ok_u<NDIM>(u, q)) ? 0 : TILE_BAD;
       if constexpr (SPEEDS) {
         const double sp = cell_speed<NDIM, T>(q, dxs);
         m = (sp > m || sp != sp) ? sp : m;
@@ -163,11 +162,15 @@ __global__ __launch_bounds__(kThreads, CUT && GATHER ? 2 : 4) void stage2d_kerne
     for (int c = 0; c < NC; c++) sq[c * QROW + e] = T(q[c]);
   }
   if constexpr (SPEEDS) wave_max_bits(m, s_red);
-  if (bad) s_status = ST_NONPHYSICAL;
-  if (far) s_far = 1;
+  s_notes.note(found);
   __syncthreads();
   __builtin_amdgcn_s_setprio(0);
-  if (g.stats && tid == 0 && s_status != ST_OK) atomicExch(&g.stats->status, s_status);
+  const int notes = s_notes.all();
+  if (notes & TILE_SKIP) {
+    if (SPEEDS && tid == 0) g.cflp[blockIdx.x] = 0ull;
+    return;
+  }
+  if (g.stats && tid == 0 && (notes & TILE_BAD)) atomicExch(&g.stats->status, ST_NONPHYSICAL);
   if constexpr (SPEEDS) {
     if (tid == 0) {
       unsigned long long b = s_red[0];
@@ -178,7 +181,56 @@ __global__ __launch_bounds__(kThreads, CUT && GATHER ? 2 : 4) void stage2d_kerne
 
   int my3[2] = {0, 0}, my1[2] = {0, 0}, mys[2] = {0, 0};
   const int wts = kernel_weights<CUT>(g.weights);
-  const TileState tile{!__builtin_amdgcn_readfirstlane(s_far) && eps_in_range(g.eps)};
+  const TileState tile{!(notes & TILE_FAR) && eps_in_range(g.eps)};
+  const int cy = tid >> 4, cx = tid & 15;  // the lane's cell (cx < 15) and x face
+  const bool mine = cx < TX && gx0 + cx < nx && gy0 + cy < ny;
+  const int64_t mycell = (gy0 + cy) * nx + gx0 + cx;
+  // the output step of the lane's cell, component kc, from its L and the
+  // stage input there (fetched where the caller does not have it)
+  auto put = [&](int kc, double L, auto uin) {
+    const int64_t o = kc * N + mycell;
+    if (MODE == OUT_RHS || MODE == OUT_RK1L) {
+      g.Rout[o] = L;
+    } else {
+      const double h = *g.dt;
+      if (MODE == OUT_RK1) {
+        g.Uout[o] = g.U0[o] + h * L;
+      } else if (MODE == OUT_RK2) {
+        g.Uout[o] = 0.75 * g.U0[o] + 0.25 * (uin(o) + h * L);
+      } else if (MODE == OUT_RK2L) {
+        const double u0 = g.U0[o];
+        g.Uout[o] = 0.75 * u0 + 0.25 * (uin(o) + h * L);
+      } else {
+        g.Uout[o] = (1.0 / 3.0) * g.U0[o] + (2.0 / 3.0) * (uin(o) + h * L);
+      }
+    }
+  };
+  // a uniform tile (steady_state): every face has the same flux
+  if (!(notes & TILE_MIXED)) {
+    double q[NC];
+    cons_prim<NDIM, T>(ref, q);
+    if (steady_state<NDIM>(q)) {
+      if (mine) {
+#pragma unroll
+        for (int kc = 0; kc < NC; kc++) {
+          const double t = steady_term(kc >= 4, q[kc]);
+          put(kc, t + t, [&](int64_t) { return ref[kc]; });
+        }
+      }
+      if (g.shortcut && (sizeof(T) == 4 || g.eps > 0.0)) {
+        // measurement only: every field-side of the tile's faces, each face
+        // counted once (in the tile after it)
+        const int64_t w = nx - gx0 < TX ? nx - gx0 : TX, h = ny - gy0 < TY ? ny - gy0 : TY;
+        if (tid == 0) {
+          atomicAdd(&g.shortcut[(blockIdx.x & 255) * 3],
+                    (unsigned long long)((w + (gx0 + w == nx)) * h * 2 * NC));
+          atomicAdd(&g.shortcut[(blockIdx.x & 255) * 3 + 1],
+                    (unsigned long long)((h + (gy0 + h == ny)) * w * 2 * NC));
+        }
+      }
+      return;
+    }
+  }
   const Div64<T> bydx(g.dx[0]), bydy(g.dx[1]);
   auto xstencil = [&](int f) {  // x face (f % 16, f / 16)
     LdsStencil2<T> st;
@@ -266,7 +318,6 @@ __global__ __launch_bounds__(kThreads, CUT && GATHER ? 2 : 4) void stage2d_kerne
 
   // 3. x faces: lane tid holds face (cx, cy), between cells cx-1 and cx of
   // row cy, and, for cx < 15, cell (cx, cy)
-  const int cy = tid >> 4, cx = tid & 15;
   double F[NC], us = 0.0;
 #pragma unroll
   for (int kk = 0; kk < NC; kk++) F[kk] = 0.0;
@@ -344,8 +395,7 @@ __global__ __launch_bounds__(kThreads, CUT && GATHER ? 2 : 4) void stage2d_kerne
   // x terms of eqs. (5)-(6) (for the x axis face order and axis order
   // coincide), plus the y terms (face order -> axis order: u_n = v is
   // component 2, u_t = u component 1), then the output step
-  if (cx < TX && gx0 + cx < nx && gy0 + cy < ny) {
-    const int64_t cell = (gy0 + cy) * nx + gx0 + cx;
+  if (mine) {
     const int fb = cy * TX + cx, fa = fb + TX;  // the cell's lower and upper y faces
     double rx[NC];
 #pragma unroll
@@ -365,24 +415,10 @@ __global__ __launch_bounds__(kThreads, CUT && GATHER ? 2 : 4) void stage2d_kerne
         const double phi = sq[kc * QROW + (cy + 3) * SX + cx + 3];
         r = r + bydy(phi * (double(sfy[NC * NFY + fa]) - double(sfy[NC * NFY + fb])));
       }
-      const double L = rx[kc] + r;
-      const int64_t o = kc * N + cell;
-      if (MODE == OUT_RHS || MODE == OUT_RK1L) {
-        g.Rout[o] = L;
-      } else {
-        const double h = *g.dt;
-        if (MODE == OUT_RK1) {
-          g.Uout[o] = g.U0[o] + h * L;
-        } else if (MODE == OUT_RK2) {
-          g.Uout[o] = 0.75 * g.U0[o] + 0.25 * (g.Uin[o] + h * L);
-        } else if (MODE == OUT_RK2L) {
-          // the stage input U0 + dt R, formed as stage 1 would have written it
-          const double u0 = g.U0[o];
-          g.Uout[o] = 0.75 * u0 + 0.25 * ((u0 + h * g.R[o]) + h * L);
-        } else {
-          g.Uout[o] = (1.0 / 3.0) * g.U0[o] + (2.0 / 3.0) * (g.Uin[o] + h * L);
-        }
-      }
+      put(kc, rx[kc] + r, [&](int64_t o) {
+        if constexpr (FROM_L) return g.U0[o] + h1 * g.R[o];  // as stage 1 would have written it
+        else return g.Uin[o];
+      });
     }
   }
 }

@@ -201,10 +201,10 @@ __device__ __forceinline__ bool cell_ok_u(const double* u, const double* q) {
 // every component.
 template <int NDIM>
 __device__ __forceinline__ bool in_range(const double* q) {
-  bool ok = q[0] >= 0x1p-20 && q[0] <= 0x1p30 && fabs(q[1 + NDIM]) <= 0x1p40 &&
-            q[2 + NDIM] >= 0x1p-10 && q[2 + NDIM] <= 0x1p10 && fabs(q[3 + NDIM]) <= 0x1p40;
+  bool ok = (q[0] >= 0x1p-20) & (q[0] <= 0x1p30) & (fabs(q[1 + NDIM]) <= 0x1p40) &
+            (q[2 + NDIM] >= 0x1p-10) & (q[2 + NDIM] <= 0x1p10) & (fabs(q[3 + NDIM]) <= 0x1p40);
 #pragma unroll
-  for (int a = 0; a < NDIM; a++) ok = ok && fabs(q[1 + a]) <= 0x1p24;
+  for (int a = 0; a < NDIM; a++) ok &= fabs(q[1 + a]) <= 0x1p24;
   return ok;
 }
 
@@ -212,6 +212,84 @@ __device__ __forceinline__ bool in_range(const double* q) {
 template <int NDIM>
 __device__ __forceinline__ bool c2_positive(const double* q) {
   return (q[2 + NDIM] + 1.0) * q[1 + NDIM] + q[3 + NDIM] > 0.0;
+}
+
+// Uniform tiles.  Where every cell a tile reads holds one state (the fluid
+// ahead of a front, the inside of a body), all its faces have one flux and
+// one interface velocity, so each difference of eqs. (5)-(6) is x - x = +0
+// and the axis' terms are the signed zeros below: the same bits without a
+// face.  Cells are compared by their bits while they are staged (a mirrored
+// ghost counts as different).  The state must be one whose flux is finite and
+// whose reconstruction passes the positivity check whatever its rounding, in
+// either arithmetic: steady_state bounds density and Gamma, keeps the stiff
+// pressure (Gamma+1) p + Pi away from cancellation, the sound speed in
+// [2^-10, 2^16] and the Mach number below 2^6 -- a rounding of 2^-24 then
+// moves no reconstructed density or stiff pressure by more than 2^-12 of it.
+// Such a tile costs its loads and stores (1024x512 at the start of a run, nine
+// tenths of it uniform: 45 us a stage against 69; fully mixed states pay one
+// comparison per staged cell, below what two runs differ by).
+template <int NDIM>
+__device__ __forceinline__ bool steady_state(const double* q) {
+  const double rho = q[0], p = q[1 + NDIM], G = q[2 + NDIM], P = q[3 + NDIM];
+  const double stiff = (G + 1.0) * p + P, gr = G * rho;
+  bool ok = rho >= 0x1p-12 && rho <= 0x1p12 && G >= 0x1p-6 && G <= 0x1p6 &&
+            fabs(p) <= 0x1p36 && fabs(P) <= 0x1p36 &&
+            stiff >= 0x1p-4 * ((G + 1.0) * fabs(p) + fabs(P)) && stiff >= 0x1p-20 * gr &&
+            stiff <= 0x1p32 * gr;
+#pragma unroll
+  for (int a = 0; a < NDIM; a++) ok = ok && gr * q[1 + a] * q[1 + a] <= 0x1p12 * stiff;
+  return ok;
+}
+
+// One axis' terms of eqs. (5)-(6) for a cell between two faces of the same
+// flux and u*: -(x - x) / dx, and for Gamma and Pi + phi (x - x) / dx.
+__device__ __forceinline__ double steady_term(bool material, double phi) {
+  return material ? -0.0 + phi * 0.0 : -0.0;
+}
+
+// What a workgroup's waves found while staging a tile: bits TILE_*, gathered
+// per lane in one register and per wave in one word (no word has to be
+// cleared first, so nothing waits before the loads).  note() is called by
+// every lane of a wave before the barrier that ends the staging, all() after
+// it, with the same result in every lane.
+enum { TILE_BAD = 1, TILE_FAR = 2, TILE_MIXED = 4, TILE_SKIP = 8 };
+template <int NWAVES>
+struct TileNotes {
+  int word[NWAVES];
+  __device__ __forceinline__ void note(int found) {
+    int w = 0;
+#pragma unroll
+    for (int b = 1; b <= TILE_SKIP; b *= 2) w |= __any(found & b) ? b : 0;
+    if ((threadIdx.x & 63) == 0) word[threadIdx.x >> 6] = w;
+  }
+  __device__ __forceinline__ int all() const {
+    int w = 0;
+#pragma unroll
+    for (int k = 0; k < NWAVES; k++) w |= word[k];
+    return __builtin_amdgcn_readfirstlane(w);
+  }
+};
+
+// Whether an earlier evaluation latched a failure (sticky).  One lane of a
+// workgroup asks, so that all its lanes agree; a plain load, issued beside
+// the staging loads: a latch of the running launch may be seen or not.
+__device__ __forceinline__ bool latched(const StatsDev* stats) {
+  return stats && __hip_atomic_load(&stats->status, __ATOMIC_RELAXED,
+                                    __HIP_MEMORY_SCOPE_WORKGROUP) != ST_OK;
+}
+
+// Whether a lane's cell differs from the tile's reference, by bits; where
+// some cell of the wave differs in its density the others are not compared
+// (a tile needs one difference).
+template <int N>
+__device__ __forceinline__ bool differs(const double* u, const double* ref, bool flip) {
+  bool d = flip | (__double_as_longlong(u[0]) != __double_as_longlong(ref[0]));
+  if (!__any(d)) {
+#pragma unroll
+    for (int c = 1; c < N; c++)
+      d |= __double_as_longlong(u[c]) != __double_as_longlong(ref[c]);
+  }
+  return d;
 }
 
 // What a workgroup knows of its whole staged tile when it starts on the

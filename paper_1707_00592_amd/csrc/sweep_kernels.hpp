@@ -65,17 +65,67 @@ struct Geo {
 // of kSweepRun consecutive tiles, the runs of the 8 XCDs interleaved (the
 // work of a front stays spread over the XCDs); tiles past the last whole
 // group of 8 runs keep their own number.  A bijection of [0, ntiles).
-constexpr int64_t kSweepRun = 64;
-__device__ __forceinline__ int64_t sweep_tile(int64_t b, int64_t ntiles) {
-  const int64_t whole = ntiles / (8 * kSweepRun) * (8 * kSweepRun);
+constexpr unsigned kSweepRun = 64;
+__device__ __forceinline__ unsigned sweep_tile(unsigned b, unsigned ntiles) {
+  const unsigned whole = ntiles / (8 * kSweepRun) * (8 * kSweepRun);
   if (b >= whole) return b;
-  const int64_t xcd = b & 7, k = b >> 3;
+  const unsigned xcd = b & 7, k = b >> 3;
   return ((k / kSweepRun) * 8 + xcd) * kSweepRun + k % kSweepRun;
+}
+
+// The output step of one cell's component (offset o into the state) from r,
+// this axis' term; uin(o) is the stage input there.
+template <int MODE, bool READ_R, class F>
+__device__ __forceinline__ void sweep_put(const SweepArgs& g, int64_t o, double r, F uin) {
+  const double L = READ_R ? g.R[o] + r : r;
+  if (MODE == OUT_PARTIAL || MODE == OUT_PARTIAL_S || MODE == OUT_RHS) {
+    g.Rout[o] = L;
+  } else {
+    const double h = *g.dt;
+    if (MODE == OUT_RK1) {
+      g.Uout[o] = g.U0[o] + h * L;
+    } else if (MODE == OUT_RK2) {
+      g.Uout[o] = 0.75 * g.U0[o] + 0.25 * (uin(o) + h * L);
+    } else {
+      g.Uout[o] = (1.0 / 3.0) * g.U0[o] + (2.0 / 3.0) * (uin(o) + h * L);
+    }
+  }
+}
+
+// A sweep's cells of a uniform tile (steady_state) whose every cell holds
+// ref: no face is evaluated and the stage input is not read again.
+template <typename T, int NDIM, int D, int TL, int TW, int NTHR, int MODE, bool READ_R, class G>
+__device__ __forceinline__ bool sweep_steady(const SweepArgs& g, const G& geo, int64_t l0,
+                                             int64_t a0, int64_t tt, int64_t N,
+                                             const double* ref) {
+  constexpr int NC = 4 + NDIM;
+  double q[NC];
+  cons_prim<NDIM, T>(ref, q);
+  if (!steady_state<NDIM>(q)) return false;
+  for (int e = threadIdx.x; e < TW * TL; e += NTHR) {
+    const int w = D == 0 ? e / TL : e % TW;
+    const int j = D == 0 ? e % TL : e / TW;
+    if (a0 + w >= geo.nA || l0 + j >= geo.nL) continue;
+    const int64_t cell = (a0 + w) * geo.sA + (l0 + j) * geo.sL + tt * geo.sT;
+#pragma unroll
+    for (int c = 0; c < NC; c++)
+      sweep_put<MODE, READ_R>(g, c * N + cell, steady_term(c >= NC - 2, q[c]),
+                              [&](int64_t) { return ref[c]; });
+  }
+  if (g.shortcut && threadIdx.x == 0 && (sizeof(T) == 4 || g.eps > 0.0)) {
+    // measurement only: every field-side of the tile's faces, each face
+    // counted once (in the tile after it)
+    const int64_t l = geo.nL - l0 < TL ? geo.nL - l0 : TL, w = geo.nA - a0 < TW ? geo.nA - a0 : TW;
+    atomicAdd(&g.shortcut[(blockIdx.x & 255) * 3 + D],
+              (unsigned long long)((l + (l0 + l == geo.nL)) * w * 2 * NC));
+  }
+  return true;
 }
 
 template <typename T, int NDIM, int D, int TL, int TW, int NTHR, int MODE,
           bool READ_R, bool CUT>
-__global__ __launch_bounds__(NTHR, MODE == OUT_PARTIAL_S ? 5 : 1) void sweep_kernel(SweepArgs g) {
+__global__ __launch_bounds__(NTHR, MODE == OUT_PARTIAL_S ? 5 : 1)
+    void sweep_kernel(SweepArgs g) {
   constexpr int NC = 4 + NDIM;
   constexpr int NP = TL + 6;     // staged positions along D
   constexpr int NF = TL + 1;     // faces along D per tile row
@@ -100,36 +150,22 @@ __global__ __launch_bounds__(NTHR, MODE == OUT_PARTIAL_S ? 5 : 1) void sweep_ker
   __shared__ __attribute__((aligned(16))) unsigned char lds[LDS_BYTES];
   T* const sq = reinterpret_cast<T*>(lds);
   T* const sf = reinterpret_cast<T*>(lds + SF_OFF);
-  __shared__ int s_status;
-  __shared__ int s_far;  // a staged cell was not in_range
-  __shared__ int s_skip;
+  __shared__ TileNotes<NTHR / 64> s_notes;
   // OUT_PARTIAL_S: this x sweep also finds its tile's max wave speed (the
   // step's time step; the tiles of an x sweep hold every cell once)
   constexpr bool SPEEDS = MODE == OUT_PARTIAL_S;
   __shared__ unsigned long long s_red[SPEEDS ? NTHR / 64 : 1];
 
   const Geo<NDIM, D> geo(g.n);
-  const int64_t ntl = (geo.nL + TL - 1) / TL;
-  const int64_t nta = (geo.nA + TW - 1) / TW;
-  const int64_t bid = sweep_tile(blockIdx.x, ntl * nta * geo.nT);
-  const int64_t tl = bid % ntl;
-  const int64_t rest = bid / ntl;
-  const int64_t ta = rest % nta;
-  const int64_t tt = rest / nta;
-  const int64_t l0 = tl * TL, a0 = ta * TW;
+  // (tile numbers fit 31 bits, as the launch does)
+  const unsigned ntl = (unsigned)((geo.nL + TL - 1) / TL);
+  const unsigned nta = (unsigned)((geo.nA + TW - 1) / TW);
+  const unsigned bid = sweep_tile(blockIdx.x, ntl * nta * (unsigned)geo.nT);
+  const unsigned rest = bid / ntl, tile_t = rest / nta;
+  const int64_t l0 = (int64_t)(bid - rest * ntl) * TL, a0 = (int64_t)(rest - tile_t * nta) * TW;
+  const int64_t tt = tile_t;
   const int64_t N = g.n[0] * g.n[1] * g.n[2];
   const int tid = threadIdx.x;
-  if (tid == 0) {
-    s_status = ST_OK;
-    s_far = 0;
-    // sticky failure: one read per workgroup so that all lanes agree
-    s_skip = g.stats ? (__atomic_load_n(&g.stats->status, __ATOMIC_RELAXED) != ST_OK) : 0;
-  }
-  __syncthreads();
-  if (s_skip) {
-    if (SPEEDS && tid == 0) g.cflp[blockIdx.x] = 0ull;
-    return;
-  }
 
   auto lidx = [](int c, int w, int p) {
     const int r = !ALIAS ? c : c >= NC - 2 ? c - (NC - 2) : c + 2;
@@ -144,9 +180,13 @@ __global__ __launch_bounds__(NTHR, MODE == OUT_PARTIAL_S ? 5 : 1) void sweep_ker
   // (the float sweeps ran slower with it)
   if constexpr (sizeof(T) == 8) __builtin_amdgcn_s_setprio(1);
   // 1. stage primitives (FP64) with ghost cells
-  bool bad = false, far = false;
+  int found = tid == 0 && latched(g.stats) ? TILE_SKIP : 0;
   double m = 0.0;  // SPEEDS: the lane's max wave speed
   const double dxs[3] = {g.dx[0], g.dx[1], g.dx[2]};
+  double ref[NC];  // the tile's first cell
+#pragma unroll
+  for (int c = 0; c < NC; c++)
+    ref[c] = g.Uin[c * N + a0 * geo.sA + l0 * geo.sL + tt * geo.sT];
   for (int e = tid; e < TW * NP; e += NTHR) {
     const int w = D == 0 ? e / NP : e % TW;
     const int p = D == 0 ? e % NP : e / TW;
@@ -159,11 +199,12 @@ __global__ __launch_bounds__(NTHR, MODE == OUT_PARTIAL_S ? 5 : 1) void sweep_ker
     double u[NC], q[NC];
 #pragma unroll
     for (int c = 0; c < NC; c++) u[c] = g.Uin[c * N + cell];
+    found |= differs<NC>(u, ref, flip) ? TILE_MIXED : 0;
     cons_prim<NDIM, T>(u, q);
-    const bool inr = in_range<NDIM>(q);
-    far = far || !inr;
+    const bool inr = sizeof(T) == 8 && in_range<NDIM>(q);
+    if constexpr (sizeof(T) == 8) found |= inr ? 0 : TILE_FAR;
     if (p >= 3 && p < 3 + TL && l < geo.nL) {
-      bad = bad || !(inr ? c2_positive<NDIM>(q) : cell_ok_u<NDIM>(u, q));
+      found |= (inr ? c2_positive<NDIM>(q) : cell_ok_u<NDIM>(u, q)) ? 0 : TILE_BAD;
       if constexpr (SPEEDS) {
         const double sp = cell_speed<NDIM, T>(q, dxs);
         m = (sp > m || sp != sp) ? sp : m;
@@ -174,10 +215,15 @@ __global__ __launch_bounds__(NTHR, MODE == OUT_PARTIAL_S ? 5 : 1) void sweep_ker
     for (int c = 0; c < NC; c++) sq[lidx(c, w, p)] = T(q[c]);
   }
   if constexpr (SPEEDS) wave_max_bits(m, s_red);
-  if (bad) s_status = ST_NONPHYSICAL;
-  if (far) s_far = 1;
+  s_notes.note(found);
   __syncthreads();
   if constexpr (sizeof(T) == 8) __builtin_amdgcn_s_setprio(0);
+  const int notes = s_notes.all();
+  if (notes & TILE_SKIP) {
+    if (SPEEDS && tid == 0) g.cflp[blockIdx.x] = 0ull;
+    return;
+  }
+  if (g.stats && tid == 0 && (notes & TILE_BAD)) atomicExch(&g.stats->status, ST_NONPHYSICAL);
   if constexpr (SPEEDS) {
     if (tid == 0) {
       unsigned long long b = s_red[0];
@@ -186,9 +232,13 @@ __global__ __launch_bounds__(NTHR, MODE == OUT_PARTIAL_S ? 5 : 1) void sweep_ker
     }
   }
 
+  if (!(notes & TILE_MIXED) &&
+      sweep_steady<T, NDIM, D, TL, TW, NTHR, MODE, READ_R>(g, geo, l0, a0, tt, N, ref))
+    return;
+
   // 2. faces: thread tid owns face (w, j); with ALIAS the values wait in
   // registers until every face has read sq
-  const TileState tile{!__builtin_amdgcn_readfirstlane(s_far) && eps_in_range(g.eps)};
+  const TileState tile{!(notes & TILE_FAR) && eps_in_range(g.eps)};
   int my3 = 0, my1 = 0, mys = 0;
   // FP64 x tiles of 8 rows x 32 faces: each wave takes an 8 x 8 block, so a
   // front across x splits fewer waves between the linear-weight form and
@@ -245,7 +295,6 @@ __global__ __launch_bounds__(NTHR, MODE == OUT_PARTIAL_S ? 5 : 1) void sweep_ker
       atomicAdd(&g.shortcut[(blk & 255) * 3 + D], (unsigned long long)ws);
   }
   __syncthreads();
-  if (g.stats && tid == 0 && s_status != ST_OK) atomicExch(&g.stats->status, s_status);
 
   // 3. cells
   const Div64<T> bydx(g.dx[D]);
@@ -264,20 +313,7 @@ __global__ __launch_bounds__(NTHR, MODE == OUT_PARTIAL_S ? 5 : 1) void sweep_ker
         const double phi = sq[lidx(kc, w, j + 3)];
         r = r + bydx(phi * (double(sf[fidx(NC, w, j + 1)]) - double(sf[fidx(NC, w, j)])));
       }
-      double L = READ_R ? g.R[kc * N + cell] + r : r;
-      const int64_t o = kc * N + cell;
-      if (MODE == OUT_PARTIAL || MODE == OUT_PARTIAL_S || MODE == OUT_RHS) {
-        g.Rout[o] = L;
-      } else {
-        const double h = *g.dt;
-        if (MODE == OUT_RK1) {
-          g.Uout[o] = g.U0[o] + h * L;
-        } else if (MODE == OUT_RK2) {
-          g.Uout[o] = 0.75 * g.U0[o] + 0.25 * (g.Uin[o] + h * L);
-        } else {
-          g.Uout[o] = (1.0 / 3.0) * g.U0[o] + (2.0 / 3.0) * (g.Uin[o] + h * L);
-        }
-      }
+      sweep_put<MODE, READ_R>(g, kc * N + cell, r, [&](int64_t o) { return g.Uin[o]; });
     }
   }
 }
@@ -296,35 +332,20 @@ __global__ __launch_bounds__(NTHR) void sweep_mlp_kernel(SweepArgs g) {
   // face fluxes in the arithmetic's type: the float form's fluxes are
   // float values, so float storage is exact and frees LDS for occupancy
   __shared__ T sf[(NC + 1) * TW * NF];
-  __shared__ int s_status;
-  __shared__ int s_skip;
+  __shared__ TileNotes<NTHR / 64> s_notes;
   // learned weights: network + one inference tile per wave
   __shared__ MlpLds mW[1];
   __shared__ MlpBiasLds mB[1];
 
   const Geo<NDIM, D> geo(g.n);
-  const int64_t ntl = (geo.nL + TL - 1) / TL;
-  const int64_t bid = blockIdx.x;
-  const int64_t tl = bid % ntl;
-  const int64_t rest = bid / ntl;
-  const int64_t nta = (geo.nA + TW - 1) / TW;
-  const int64_t ta = rest % nta;
-  const int64_t tt = rest / nta;
-  const int64_t l0 = tl * TL, a0 = ta * TW;
+  const unsigned ntl = (unsigned)((geo.nL + TL - 1) / TL);
+  const unsigned nta = (unsigned)((geo.nA + TW - 1) / TW);
+  const unsigned rest = blockIdx.x / ntl, tile_t = rest / nta;
+  const int64_t l0 = (int64_t)(blockIdx.x - rest * ntl) * TL;
+  const int64_t a0 = (int64_t)(rest - tile_t * nta) * TW, tt = tile_t;
   const int64_t N = g.n[0] * g.n[1] * g.n[2];
   const int tid = threadIdx.x;
-  if (tid == 0) {
-    s_status = ST_OK;
-    // sticky failure: one read per workgroup so that all lanes agree
-    s_skip = g.stats ? (__atomic_load_n(&g.stats->status, __ATOMIC_RELAXED) != ST_OK) : 0;
-  }
   mlp_stage_bf16(*mW, g.mlp, tid, NTHR);
-  __syncthreads();
-  mlp_bias_stage(*mB, *mW, tid, NTHR);
-  MlpRegs regs;
-  mlp_regs_load(*mW, regs);
-  __syncthreads();
-  if (s_skip) return;
 
   auto lidx = [](int c, int w, int p) {
     return D == 0 ? (c * TW + w) * NP + p : (c * NP + p) * TW + w;
@@ -334,7 +355,11 @@ __global__ __launch_bounds__(NTHR) void sweep_mlp_kernel(SweepArgs g) {
   };
 
   // 1. stage primitives (FP64) with ghost cells
-  bool bad = false;
+  int found = tid == 0 && latched(g.stats) ? TILE_SKIP : 0;
+  double ref[NC];  // the tile's first cell
+#pragma unroll
+  for (int c = 0; c < NC; c++)
+    ref[c] = g.Uin[c * N + a0 * geo.sA + l0 * geo.sL + tt * geo.sT];
   for (int e = tid; e < TW * NP; e += NTHR) {
     const int w = D == 0 ? e / NP : e % TW;
     const int p = D == 0 ? e % NP : e / TW;
@@ -344,14 +369,28 @@ __global__ __launch_bounds__(NTHR) void sweep_mlp_kernel(SweepArgs g) {
     bool flip;
     const int64_t li = bc_index(l, geo.nL, g.bc_lo, g.bc_hi, flip);
     const int64_t cell = a * geo.sA + li * geo.sL + tt * geo.sT;
-    double q[NC];
-    cell_prim<NDIM, T>(g.Uin, N, cell, q);
-    if (p >= 3 && p < 3 + TL && l < geo.nL) bad = bad || !cell_ok<NDIM>(g.Uin, N, cell, q);
+    double u[NC], q[NC];
+#pragma unroll
+    for (int c = 0; c < NC; c++) u[c] = g.Uin[c * N + cell];
+    found |= differs<NC>(u, ref, flip) ? TILE_MIXED : 0;
+    cons_prim<NDIM, T>(u, q);
+    if (p >= 3 && p < 3 + TL && l < geo.nL) found |= cell_ok_u<NDIM>(u, q) ? 0 : TILE_BAD;
     if (flip) q[1 + D] = -q[1 + D];
 #pragma unroll
     for (int c = 0; c < NC; c++) sq[lidx(c, w, p)] = T(q[c]);
   }
-  if (bad) s_status = ST_NONPHYSICAL;
+  s_notes.note(found);
+  __syncthreads();
+  const int notes = s_notes.all();
+  if (notes & TILE_SKIP) return;
+  if (g.stats && tid == 0 && (notes & TILE_BAD)) atomicExch(&g.stats->status, ST_NONPHYSICAL);
+  if (!(notes & TILE_MIXED) &&
+      sweep_steady<T, NDIM, D, TL, TW, NTHR, MODE, READ_R>(g, geo, l0, a0, tt, N, ref))
+    return;
+  // the network: registers and biases from the parameters staged above
+  mlp_bias_stage(*mB, *mW, tid, NTHR);
+  MlpRegs regs;
+  mlp_regs_load(*mW, regs);
   __syncthreads();
 
   // 2. faces: the trip count is the same for every lane (see above)
@@ -399,7 +438,6 @@ __global__ __launch_bounds__(NTHR) void sweep_mlp_kernel(SweepArgs g) {
     if (mr.fallbacks) atomicAdd(&g.stats->mlp_fallback[D], (unsigned long long)mr.fallbacks);
   }
   __syncthreads();
-  if (g.stats && tid == 0 && s_status != ST_OK) atomicExch(&g.stats->status, s_status);
 
   // 3. cells
   const Div64<T> bydx(g.dx[D]);
@@ -418,20 +456,7 @@ __global__ __launch_bounds__(NTHR) void sweep_mlp_kernel(SweepArgs g) {
         const double phi = sq[lidx(kc, w, j + 3)];
         r = r + bydx(phi * (double(sf[fidx(NC, w, j + 1)]) - double(sf[fidx(NC, w, j)])));
       }
-      double L = READ_R ? g.R[kc * N + cell] + r : r;
-      const int64_t o = kc * N + cell;
-      if (MODE == OUT_PARTIAL || MODE == OUT_RHS) {
-        g.Rout[o] = L;
-      } else {
-        const double h = *g.dt;
-        if (MODE == OUT_RK1) {
-          g.Uout[o] = g.U0[o] + h * L;
-        } else if (MODE == OUT_RK2) {
-          g.Uout[o] = 0.75 * g.U0[o] + 0.25 * (g.Uin[o] + h * L);
-        } else {
-          g.Uout[o] = (1.0 / 3.0) * g.U0[o] + (2.0 / 3.0) * (g.Uin[o] + h * L);
-        }
-      }
+      sweep_put<MODE, READ_R>(g, kc * N + cell, r, [&](int64_t o) { return g.Uin[o]; });
     }
   }
 }
