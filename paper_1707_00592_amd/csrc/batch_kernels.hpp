@@ -77,7 +77,7 @@ __global__ __launch_bounds__(TL + 1, sizeof(T) == 4 ? 6 : 1) void batch_stage_ke
       double u[NC], q[NC];
 #pragma unroll
       for (int c = 0; c < NC; c++) u[c] = g.Uin[c * total + lo + li];
-      found |= differs<NC>(u, ref, flip) ? TILE_MIXED : 0;
+      found |= differs<NC>(u, ref, flip);
       cons_prim<1, T>(u, q);
       const bool inr = sizeof(T) == 8 && in_range<1>(q);
       if constexpr (sizeof(T) == 8) found |= inr ? 0 : TILE_FAR;
@@ -92,7 +92,9 @@ __global__ __launch_bounds__(TL + 1, sizeof(T) == 4 ? 6 : 1) void batch_stage_ke
     if constexpr (sizeof(T) == 8) __builtin_amdgcn_s_setprio(0);
     const int notes = s_notes.all();
     failed |= notes & TILE_BAD;
-    const TileState tile{!(notes & TILE_FAR) && eps_in_range(g.eps)};
+    // (one_fluid not in the float form: its registers cost more than it saves)
+    const TileState tile{!(notes & TILE_FAR) && eps_in_range(g.eps),
+                         sizeof(T) == 8 && !(notes & TILE_FLUIDS)};
     const double h = g.dt[prob];
     // the output step of a cell's component (offset o) from its L and the
     // stage input there

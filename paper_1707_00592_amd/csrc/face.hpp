@@ -350,16 +350,23 @@ __device__ __forceinline__ Ind<double> indicators_unit(const TauUnit& u, double 
   return r;
 }
 
+// The linear form on the candidates: the optimal weights of eq. (21)/(28),
+// normalised, or the cut-off's full set (W_CUTOFF divides 4, 2, 3, 1 by 10).
+template <bool CUT>
+__device__ __forceinline__ double linear_unit(const Cand& q) {
+  constexpr double s5 = ((ISW_D1 + ISW_D2) + ISW_D3) + ISW_D4;
+  constexpr double w1 = CUT ? 4.0 / 10.0 : ISW_D1 / s5, w2 = CUT ? 2.0 / 10.0 : ISW_D2 / s5,
+                   w3 = CUT ? 3.0 / 10.0 : ISW_D3 / s5, w4 = CUT ? 1.0 / 10.0 : ISW_D4 / s5;
+  return ((w1 * q.c1 + w2 * q.c2) + w3 * q.c3) + w4 * q.c4;
+}
+
 template <bool BASIC>
 __device__ __forceinline__ double weno_f64_unit(double a, double b, double c, double d, double e,
                                                 double eps, int& nlin) {
   const TauUnit t = tau_unit(a, b, c, d, e);
   if (t.tau < 0x1p-60 * eps) {
-    constexpr double s5 = ((ISW_D1 + ISW_D2) + ISW_D3) + ISW_D4;
     nlin++;
-    const Cand q = cand_unit(a, b, c, d, e);
-    return (((ISW_D1 / s5) * q.c1 + (ISW_D2 / s5) * q.c2) + (ISW_D3 / s5) * q.c3) +
-           (ISW_D4 / s5) * q.c4;
+    return linear_unit<false>(cand_unit(a, b, c, d, e));
   }
   const Ind<double> s = indicators_unit(t, a, b, c, d, e);
   Alpha al;
@@ -548,9 +555,8 @@ __device__ __forceinline__ double weno_f64_cutoff_unit(double a, double b, doubl
   const TauUnit t = tau_unit(a, b, c, d, e);
   const Cand q = cand_unit(a, b, c, d, e);
   if (t.tau < 0x1p-60 * eps) {
-    constexpr CutWeights W = make_cut_weights();
     nlin++;
-    return ((W.w[15][0] * q.c1 + W.w[15][1] * q.c2) + W.w[15][2] * q.c3) + W.w[15][3] * q.c4;
+    return linear_unit<true>(q);
   }
   const Ind<double> s = indicators_unit(t, a, b, c, d, e);
   const double* w = kCutWeights.w[cut_mask_f64<true>(s, eps, false)];

@@ -143,7 +143,7 @@ __global__ __launch_bounds__(kThreads, CUT && GATHER ? 2 : 4) void stage2d_kerne
     const int64_t cell = iy * nx + ix;
     double u[NC], q[NC];
     input(cell, u);
-    found |= differs<NC>(u, ref, flip) ? TILE_MIXED : 0;
+    found |= differs<NC>(u, ref, flip);
     cons_prim<NDIM, T>(u, q);
     const bool inr = sizeof(T) == 8 && in_range<NDIM>(q);
     if constexpr (sizeof(T) == 8) found |= inr ? 0 : TILE_FAR;
@@ -181,7 +181,7 @@ __global__ __launch_bounds__(kThreads, CUT && GATHER ? 2 : 4) void stage2d_kerne
 
   int my3[2] = {0, 0}, my1[2] = {0, 0}, mys[2] = {0, 0};
   const int wts = kernel_weights<CUT>(g.weights);
-  const TileState tile{!(notes & TILE_FAR) && eps_in_range(g.eps)};
+  const TileState tile{!(notes & TILE_FAR) && eps_in_range(g.eps), !(notes & TILE_FLUIDS)};
   const int cy = tid >> 4, cx = tid & 15;  // the lane's cell (cx < 15) and x face
   const bool mine = cx < TX && gx0 + cx < nx && gy0 + cy < ny;
   const int64_t mycell = (gy0 + cy) * nx + gx0 + cx;

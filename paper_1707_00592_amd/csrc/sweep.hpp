@@ -252,14 +252,14 @@ __device__ __forceinline__ double steady_term(bool material, double phi) {
 // cleared first, so nothing waits before the loads).  note() is called by
 // every lane of a wave before the barrier that ends the staging, all() after
 // it, with the same result in every lane.
-enum { TILE_BAD = 1, TILE_FAR = 2, TILE_MIXED = 4, TILE_SKIP = 8 };
+enum { TILE_BAD = 1, TILE_FAR = 2, TILE_MIXED = 4, TILE_SKIP = 8, TILE_FLUIDS = 16 };
 template <int NWAVES>
 struct TileNotes {
   int word[NWAVES];
   __device__ __forceinline__ void note(int found) {
     int w = 0;
 #pragma unroll
-    for (int b = 1; b <= TILE_SKIP; b *= 2) w |= __any(found & b) ? b : 0;
+    for (int b = 1; b <= TILE_FLUIDS; b *= 2) w |= __any(found & b) ? b : 0;
     if ((threadIdx.x & 63) == 0) word[threadIdx.x >> 6] = w;
   }
   __device__ __forceinline__ int all() const {
@@ -278,24 +278,26 @@ __device__ __forceinline__ bool latched(const StatsDev* stats) {
                                     __HIP_MEMORY_SCOPE_WORKGROUP) != ST_OK;
 }
 
-// Whether a lane's cell differs from the tile's reference, by bits; where
-// some cell of the wave differs in its density the others are not compared
-// (a tile needs one difference).
+// How a lane's cell differs from the tile's reference, by bits: TILE_MIXED
+// (where some cell of the wave differs in its density the others are not
+// compared: a tile needs one difference) and TILE_FLUIDS.
 template <int N>
-__device__ __forceinline__ bool differs(const double* u, const double* ref, bool flip) {
-  bool d = flip | (__double_as_longlong(u[0]) != __double_as_longlong(ref[0]));
+__device__ __forceinline__ int differs(const double* u, const double* ref, bool flip) {
+  auto ne = [&](int c) { return __double_as_longlong(u[c]) != __double_as_longlong(ref[c]); };
+  const bool f = ne(N - 2) | ne(N - 1);
+  bool d = flip | f | ne(0);
   if (!__any(d)) {
 #pragma unroll
-    for (int c = 1; c < N; c++)
-      d |= __double_as_longlong(u[c]) != __double_as_longlong(ref[c]);
+    for (int c = 1; c < N - 2; c++) d |= ne(c);
   }
-  return d;
+  return (d ? TILE_MIXED : 0) | (f ? TILE_FLUIDS : 0);
 }
 
 // What a workgroup knows of its whole staged tile when it starts on the
 // faces (the same for every lane).
 struct TileState {
-  bool fast;  // FP64: every staged cell in_range and epsilon too
+  bool fast;      // FP64: every staged cell in_range and epsilon too
+  bool one_fluid;  // Gamma and Pi are those of the tile's first cell everywhere
 };
 
 // Face-order component k -> axis-order (LDS / conservative) component.
@@ -387,7 +389,7 @@ __device__ __forceinline__ void mlp_field(const T* w, MlpRun& mr, T eps, T& rl, 
 template <typename T, int NDIM, int D, bool CUT = false, class S>
 __device__ __forceinline__ void recon(const S& st, int sides, bool order3, int weights, T eps,
                                       T a, T b, double bd, double gd, double* ql, double* qr,
-                                      int& nshort, MlpRun* mr = nullptr) {
+                                      int& nshort, MlpRun* mr = nullptr, bool one_fluid = false) {
   constexpr int NT = NDIM - 1, NC = 5 + NT;
   constexpr int CR = 0, CU = 1 + D, CP = 1 + NDIM, CG = 2 + NDIM, CPI = 3 + NDIM;
   // Fully unrolled over the fields (static register indices for the face
@@ -396,6 +398,17 @@ __device__ __forceinline__ void recon(const S& st, int sides, bool order3, int w
 #pragma unroll
   for (int m = 0; m < NC; m++) {
     __builtin_amdgcn_sched_barrier(0);
+    if constexpr (sizeof(T) == 4) {
+      // float form, one fluid in the whole tile: a stencil without spread
+      // returns its centre value on both sides
+      if ((m == 2 + NT || m == 3 + NT) && one_fluid) {
+        const double r = double(st(m == 2 + NT ? CG : CPI, 2));
+        if (m == 2 + NT) ql[3 + NT] = qr[3 + NT] = r;
+        else ql[4 + NT] = qr[4 + NT] = r;
+        nshort += 2;
+        continue;
+      }
+    }
     // row of L: 0 = acoustic (sign sa), 1 = entropy, 2 = copy of component cx
     int kind = 2, cx = CG;
     T sa = a;
@@ -483,15 +496,28 @@ __device__ __forceinline__ void back_project(int m, double r, double bd, double 
 }
 
 // 5th-order FP64 face states of a face in range, fully unrolled over the
-// fields as recon.
+// fields as recon.  Away from interfaces (one_fluid, the same for the whole
+// tile) Gamma and Pi need no stencil: two of the 5 + NT fields, whose tau5,
+// candidates and twelve LDS reads were a tenth of a face in the general form.
 template <int NDIM, int D, bool CUT, bool BASIC, class S>
-__device__ __forceinline__ void recon_fast(const S& st, double eps, double a, double b, double bd,
-                                           double gd, double* ql, double* qr, int& nshort) {
+__device__ __forceinline__ void recon_fast(const S& st, bool one_fluid, double eps, double a,
+                                           double b, double bd, double gd, double* ql, double* qr,
+                                           int& nshort) {
   constexpr int NT = NDIM - 1, NC = 5 + NT;
   constexpr int CR = 0, CU = 1 + D, CP = 1 + NDIM, CG = 2 + NDIM, CPI = 3 + NDIM;
 #pragma unroll
   for (int m = 0; m < NC; m++) {
     __builtin_amdgcn_sched_barrier(0);
+    if ((m == 2 + NT || m == 3 + NT) && one_fluid) {
+      // tau5 = 0: the candidates' linear form on six equal values, the same
+      // for both sides
+      const double v = st(m == 2 + NT ? CG : CPI, 2);
+      const double r = linear_unit<CUT>(cand_unit(v, v, v, v, v));
+      back_project<NT>(m, r, bd, gd, ql);
+      back_project<NT>(m, r, bd, gd, qr);
+      nshort += 2;
+      continue;
+    }
     double w[6];
 #pragma unroll
     for (int j = 0; j < 6; j++) {
@@ -596,8 +622,9 @@ __device__ __forceinline__ void states_flux(const double* ql, const double* qr, 
 // general reconstruction and the cascade behind a branch inside this path the
 // 2D stage took 5-8% longer on states that never reach them.
 template <int NDIM, int D, bool CUT, class S>
-__device__ __forceinline__ bool face_common(const S& st, int weights, int mood, double eps,
-                                            double* F, double& us, int& nshort) {
+__device__ __forceinline__ bool face_common(const S& st, const TileState& tile, int weights,
+                                            int mood, double eps, double* F, double& us,
+                                            int& nshort) {
   constexpr int NT = NDIM - 1, NC = 5 + NT;
   double a, b, bd, gd, ql[NC], qr[NC];
   face_params<double, NDIM>(st, a, b, bd, gd);
@@ -605,9 +632,9 @@ __device__ __forceinline__ bool face_common(const S& st, int weights, int mood, 
   // b = 1/c^2 of the mean state: c^2 >= kFaceC2Min
   bool bad = !(b > 0.0 && b <= 1.0 / kFaceC2Min);
   if (!CUT && weights == W_BASIC)
-    recon_fast<NDIM, D, CUT, true>(st, eps, a, b, bd, gd, ql, qr, nshort);
+    recon_fast<NDIM, D, CUT, true>(st, tile.one_fluid, eps, a, b, bd, gd, ql, qr, nshort);
   else
-    recon_fast<NDIM, D, CUT, false>(st, eps, a, b, bd, gd, ql, qr, nshort);
+    recon_fast<NDIM, D, CUT, false>(st, tile.one_fluid, eps, a, b, bd, gd, ql, qr, nshort);
   bad = bad || (mood && mood_fail<NT>(ql, qr));
   states_flux<double, NT>(ql, qr, F, us);
   return bad;
@@ -651,7 +678,7 @@ __device__ __forceinline__ void face_flux(const S& st, const TileState& tile, in
     bool other = true;
     n3 = 0;
     n1 = 0;
-    if (tile.fast) other = face_common<NDIM, D, CUT>(st, weights, mood, eps, F, us, nshort);
+    if (tile.fast) other = face_common<NDIM, D, CUT>(st, tile, weights, mood, eps, F, us, nshort);
     if (__any(other)) face_general<NDIM, D, CUT>(st, weights, mood, eps, F, us, n3, n1, nshort);
     return;
   } else {
@@ -665,7 +692,8 @@ __device__ __forceinline__ void face_flux(const S& st, const TileState& tile, in
     mlp_material(Gb, Pb, mr->f6, mr->f7);
   }
   nshort = 0;
-  recon<T, NDIM, D, CUT>(st, 3, false, weights, T(eps), a, b, bd, gd, ql, qr, nshort, mr);
+  recon<T, NDIM, D, CUT>(st, 3, false, weights, T(eps), a, b, bd, gd, ql, qr, nshort, mr,
+                         tile.one_fluid);
   n3 = 0;
   n1 = 0;
   if (mood) {
@@ -705,12 +733,13 @@ __device__ __forceinline__ int face_flux_first(const S& st, const TileState& til
   nshort = 0;
   if constexpr (sizeof(T) == 8) {
     if (!tile.fast) return 1;
-    return face_common<NDIM, D, CUT>(st, weights, 1, eps, F, us, nshort) ? 1 : 0;
+    return face_common<NDIM, D, CUT>(st, tile, weights, 1, eps, F, us, nshort) ? 1 : 0;
   } else {
     T a, b;
     double bd, gd, ql[NC], qr[NC];
     face_params<T, NDIM>(st, a, b, bd, gd);
-    recon<T, NDIM, D, CUT>(st, 3, false, weights, T(eps), a, b, bd, gd, ql, qr, nshort);
+    recon<T, NDIM, D, CUT>(st, 3, false, weights, T(eps), a, b, bd, gd, ql, qr, nshort, nullptr,
+                           tile.one_fluid);
     const int fail = mood_fail<NT>(ql, qr);
     if (!fail) states_flux<T, NT>(ql, qr, F, us);
     return fail;

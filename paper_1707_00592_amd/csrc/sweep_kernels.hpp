@@ -124,8 +124,7 @@ __device__ __forceinline__ bool sweep_steady(const SweepArgs& g, const G& geo, i
 
 template <typename T, int NDIM, int D, int TL, int TW, int NTHR, int MODE,
           bool READ_R, bool CUT>
-__global__ __launch_bounds__(NTHR, MODE == OUT_PARTIAL_S ? 5 : 1)
-    void sweep_kernel(SweepArgs g) {
+__global__ __launch_bounds__(NTHR, MODE == OUT_PARTIAL_S ? 5 : 1) void sweep_kernel(SweepArgs g) {
   constexpr int NC = 4 + NDIM;
   constexpr int NP = TL + 6;     // staged positions along D
   constexpr int NF = TL + 1;     // faces along D per tile row
@@ -199,7 +198,7 @@ __global__ __launch_bounds__(NTHR, MODE == OUT_PARTIAL_S ? 5 : 1)
     double u[NC], q[NC];
 #pragma unroll
     for (int c = 0; c < NC; c++) u[c] = g.Uin[c * N + cell];
-    found |= differs<NC>(u, ref, flip) ? TILE_MIXED : 0;
+    found |= differs<NC>(u, ref, flip);
     cons_prim<NDIM, T>(u, q);
     const bool inr = sizeof(T) == 8 && in_range<NDIM>(q);
     if constexpr (sizeof(T) == 8) found |= inr ? 0 : TILE_FAR;
@@ -238,7 +237,7 @@ __global__ __launch_bounds__(NTHR, MODE == OUT_PARTIAL_S ? 5 : 1)
 
   // 2. faces: thread tid owns face (w, j); with ALIAS the values wait in
   // registers until every face has read sq
-  const TileState tile{!(notes & TILE_FAR) && eps_in_range(g.eps)};
+  const TileState tile{!(notes & TILE_FAR) && eps_in_range(g.eps), !(notes & TILE_FLUIDS)};
   int my3 = 0, my1 = 0, mys = 0;
   // FP64 x tiles of 8 rows x 32 faces: each wave takes an 8 x 8 block, so a
   // front across x splits fewer waves between the linear-weight form and
@@ -372,7 +371,7 @@ __global__ __launch_bounds__(NTHR) void sweep_mlp_kernel(SweepArgs g) {
     double u[NC], q[NC];
 #pragma unroll
     for (int c = 0; c < NC; c++) u[c] = g.Uin[c * N + cell];
-    found |= differs<NC>(u, ref, flip) ? TILE_MIXED : 0;
+    found |= differs<NC>(u, ref, flip);
     cons_prim<NDIM, T>(u, q);
     if (p >= 3 && p < 3 + TL && l < geo.nL) found |= cell_ok_u<NDIM>(u, q) ? 0 : TILE_BAD;
     if (flip) q[1 + D] = -q[1 + D];
@@ -418,7 +417,7 @@ __global__ __launch_bounds__(NTHR) void sweep_mlp_kernel(SweepArgs g) {
     st.pstride = D == 0 ? 1 : TW;
     double F[NC], us;
     int n3, n1, nf;
-    face_flux<T, NDIM, D>(st, TileState{false}, g.weights, g.mood, g.eps, F, us, n3, n1, nf, &mr);
+    face_flux<T, NDIM, D>(st, TileState{false, !(notes & TILE_FLUIDS)}, g.weights, g.mood, g.eps, F, us, n3, n1, nf, &mr);
     if (!valid) continue;
     // the face on a tile boundary is evaluated by both tiles; count it once
     // (in the tile to its right, or the last tile for the domain's last face)
