@@ -193,7 +193,8 @@ ISWENO_API int isweno_cfl_dt(isweno_ctx *ctx, const isweno_grid *grid,
  * dt is a device scalar: computed from U^n and written when opts->cfl > 0
  * (the value of isweno_cfl_dt on U^n; in the FP32 form of a 2D or 3D grid
  * within a few ulp of it, its primitive recovery dividing through
- * reciprocals), read otherwise.  The step's launches are captured once into a HIP graph
+ * reciprocals), read otherwise.  The step of a 1D grid of at most 511 cells is
+ * one launch; otherwise the step's launches are captured once into a HIP graph
  * per (U, dt, stats, grid, opts) and replayed on the given stream; with
  * kernel timing enabled, or with opts->dt_max > 0, they are launched
  * directly instead.  Same results either way. */
@@ -333,7 +334,9 @@ ISWENO_API int isweno_mlp_pack(isweno_ctx *ctx, const float *params, uint16_t *p
  * recorded events and returns the total milliseconds and launch count of
  * one kind since the last enable. */
 enum {
-  ISWENO_K_SWEEP_X = 0,  /* stage sweep along x (also the whole 1D stage) */
+  ISWENO_K_SWEEP_X = 0,  /* stage sweep along x (also the whole 1D stage, and
+                            the whole step of a 1D grid of at most 511 cells,
+                            which is one launch) */
   ISWENO_K_SWEEP_Y = 1,  /* stage sweep along y */
   ISWENO_K_SWEEP_Z = 2,  /* stage sweep along z */
   ISWENO_K_CFL = 3,      /* time-step reduction */

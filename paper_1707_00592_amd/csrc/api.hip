@@ -11,6 +11,7 @@
 #include "ctx.hpp"
 #include "isweno.h"
 #include "launch.hpp"
+#include "step1d.hpp"
 #include "sweep.hpp"
 
 namespace {
@@ -280,6 +281,34 @@ hipError_t enqueue_rk3(isweno_ctx* c, const isweno_grid* g, const isweno_opts* o
   return stage(c, g, o, a, U1, isw::OUT_RK3, timed, s);
 }
 
+// A 1D line short enough for one workgroup steps in one launch, without a
+// workspace or a graph (the same kernel for every way a step is asked for, so
+// that the float form's bits do not depend on it).
+bool short_line(const isweno_grid* g, const isweno_opts* o) {
+  return g->ndim == 1 && g->n[0] <= isw::kStep1dMax && o->weights != ISWENO_W_MLP;
+}
+
+int step_short_line(isweno_ctx* c, const isweno_grid* g, const isweno_opts* o, double* U,
+                    double* dt, isweno_stats* stats, bool timed, hipStream_t s) {
+  isw::Step1dArgs a{};
+  a.U = U;
+  a.dt = dt;
+  a.stats = reinterpret_cast<isw::StatsDev*>(stats);
+  a.n = (int)g->n[0];
+  a.dx = g->dx[0];
+  a.bc_lo = g->bc_lo[0];
+  a.bc_hi = g->bc_hi[0];
+  a.weights = o->weights;
+  a.mood = o->mood;
+  a.eps = o->eps;
+  a.cfl = o->cfl;
+  a.dt_max = o->dt_max;
+  a.shortcut = timed && c->timing ? c->shortcut : nullptr;
+  KTimer t(timed ? c : nullptr, ISWENO_K_SWEEP_X);
+  return isw::launch_step1d(o->precision, a, s, t.ev) == hipSuccess ? ISWENO_OK
+                                                                    : ISWENO_ERR_DEVICE;
+}
+
 // Workspace of the context: U1 = ws, U2 = ws + nc*N, then the per-tile
 // maxima of a fused_dt step.
 size_t ws_bytes(const isweno_grid* g, const isweno_opts* o) {
@@ -428,8 +457,9 @@ int isweno_rk3_step(isweno_ctx* c, const isweno_grid* g, const isweno_opts* o, d
   if ((r = check_grid(g)) != ISWENO_OK) return r;
   if ((r = check_opts(o)) != ISWENO_OK) return r;
   if (hipSetDevice(c->device) != hipSuccess) return ISWENO_ERR_DEVICE;
-  if ((r = ensure_ws(c, ws_bytes(g, o))) != ISWENO_OK) return r;
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+  if (short_line(g, o)) return step_short_line(c, g, o, U, dt, stats, true, s);
+  if ((r = ensure_ws(c, ws_bytes(g, o))) != ISWENO_OK) return r;
   // Launch directly with kernel timing on (events bracket each kernel) and
   // when dt is clipped (dt_max > 0: a value that usually changes from call
   // to call, and a graph per value would only be captured to be dropped);
@@ -491,9 +521,10 @@ int isweno_rk3_step_noalloc(isweno_ctx* c, const isweno_grid* g, const isweno_op
       ws_bytes(g, o) > kScratchStates)
     return ISWENO_ERR_ARG;
   if (hipSetDevice(c->device) != hipSuccess) return ISWENO_ERR_DEVICE;
+  hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+  if (short_line(g, o)) return step_short_line(c, g, o, U, dt, stats, false, s);
   unsigned char* base = scratch_addr(c->device);  // resolved by isweno_create
   if (!base) return ISWENO_ERR_DEVICE;
-  hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   auto* maxbits = reinterpret_cast<unsigned long long*>(base);
   double* U1 = reinterpret_cast<double*>(base + isw::kCflWordsBytes);
   double* U2 = U1 + (size_t)nc * (size_t)N;

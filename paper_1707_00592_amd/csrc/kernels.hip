@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include "launch.hpp"
+#include "step1d.hpp"
 #include "sweep_kernels.hpp"
 
 namespace isw {
@@ -133,6 +134,12 @@ hipError_t launch_sweep(int precision, int ndim, int D, const SweepArgs& a, int 
   if (a.weights == W_CUTOFF) return launch_sweep_cut(precision, ndim, D, a, mode, readR, s, ev);
   return precision == 1 ? launch_sweep_f32(ndim, D, a, mode, readR, s, ev)
                         : launch_sweep_p<double, false, false>(ndim, D, a, mode, readR, s, ev);
+}
+
+hipError_t launch_step1d(int precision, const Step1dArgs& a, hipStream_t s, LaunchEvents ev) {
+  if (a.weights == W_MLP) return hipErrorInvalidValue;
+  if (precision == 1) return launch_step1d_f32(a, s, ev);
+  return a.weights == W_CUTOFF ? launch_step1d_cut(a, s, ev) : launch_step1d_t<double, false>(a, s, ev);
 }
 
 __global__ void zero_cfl_kernel(unsigned long long* w) {

@@ -8,6 +8,7 @@ namespace isw {
 
 struct SweepArgs;
 struct BatchArgs;
+struct Step1dArgs;
 
 // Optional timing events: when set, the launch itself records the start of
 // its (first) kernel into start and the end of its (last) kernel into stop.
@@ -36,6 +37,17 @@ hipError_t launch_sweep_f32(int ndim, int D, const SweepArgs& a, int mode, bool 
                             hipStream_t s, LaunchEvents ev);
 hipError_t launch_sweep_cut_f32(int ndim, int D, const SweepArgs& a, int mode, bool readR,
                                 hipStream_t s, LaunchEvents ev);
+
+// A whole RK3 step of a 1D line of at most kStep1dMax cells in one launch (not
+// for the learned weights).  Its one workgroup gains over four launches of
+// spread-out workgroups as long as its SIMDs hold two waves each: 200 cells
+// 39 -> 24 us a step, 511 cells 41 -> 31 us (float 28 -> 15, 30 -> 17 us); at
+// 1023 cells (four waves each) the FP64 step would take longer than the launches.
+constexpr int64_t kStep1dMax = 511;
+hipError_t launch_step1d(int precision, const Step1dArgs& a, hipStream_t s,
+                         LaunchEvents ev = {});
+hipError_t launch_step1d_cut(const Step1dArgs& a, hipStream_t s, LaunchEvents ev);
+hipError_t launch_step1d_f32(const Step1dArgs& a, hipStream_t s, LaunchEvents ev);
 
 // Bytes of the time-step words (the max and the ticket).
 constexpr size_t kCflWordsBytes = 256;
