@@ -238,8 +238,8 @@ ISWENO_API int isweno_batch_plan_create(isweno_ctx *ctx, int32_t nprob,
 ISWENO_API void isweno_batch_plan_destroy(isweno_batch_plan *plan);
 
 /* Times every tile configuration on a scratch copy of U (device) and keeps
- * the fastest for this plan; *chosen_tile (may be NULL) receives the tile
- * length picked.  Synchronises the stream. */
+ * the fastest for this plan; *chosen_tile (may be NULL) receives the lanes
+ * per tile picked, less one (63, 127 or 255).  Synchronises the stream. */
 ISWENO_API int isweno_batch_autotune(isweno_ctx *ctx, isweno_batch_plan *plan,
                           const isweno_opts *opts, const double *U,
                           int32_t *chosen_tile, void *stream);
@@ -254,7 +254,8 @@ ISWENO_API int isweno_batch_autotune(isweno_ctx *ctx, isweno_batch_plan *plan,
  * values are then unspecified) and the problem is not advanced afterwards,
  * while the other problems go on.  stats (may be NULL) gets the MOOD
  * counters and, when any problem failed, ISWENO_ERR_NONPHYSICAL.  Each step
- * is one HIP graph launch (per-problem start-of-step kernel plus three
+ * is one HIP graph launch (a per-problem start-of-step kernel, then one kernel
+ * that carries every tile through the step; with a periodic end three
  * persistent stage kernels), instantiated on first use for this (plan, U,
  * dt, stats, status, opts) and replayed afterwards. */
 ISWENO_API int isweno_batch_step(isweno_ctx *ctx, isweno_batch_plan *plan,

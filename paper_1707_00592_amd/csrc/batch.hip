@@ -1,15 +1,18 @@
 // Many independent 1D problems of uneven length (isweno_batch_*).
 //
 // Layout: U[c * total + cell], problem p owns cells offsets[p] ..
-// offsets[p+1]-1.  Each RK stage is ONE persistent launch: a grid of
-// (compute units x blocks per CU) workgroups walks a static list of tiles
-// (a tile = up to TL consecutive cells of one problem) in round-robin order,
-// so the assignment is deterministic and the launch count does not grow
-// with the number of problems.  Ghost cells come from each problem's own
-// boundary conditions while loading, so tiles never straddle problems.
-// One RK3 step (per-problem time step + three stages) is captured once into
-// a HIP graph and replayed.  The tile length TL and the grid size are chosen
-// by timing every candidate on the caller's data (isweno_batch_autotune).
+// offsets[p+1]-1.  A step is two launches: one workgroup per problem forms its
+// time step and copies the cells next to tile ends, then one workgroup per
+// tile carries its tile through the three stages in place
+// (batch_step_kernel).  Plans with a periodic end run one PERSISTENT launch
+// per stage instead: a grid of (compute units x blocks per CU) workgroups
+// walks a static list of tiles in round-robin order, so the assignment is
+// deterministic and the launch count does not grow with the number of
+// problems.  Ghost cells come from each problem's own boundary conditions, so
+// tiles never straddle problems.  A step is captured once into a HIP graph and
+// replayed.  The lanes per tile (and the grid size of the stage launches) are
+// chosen by timing every candidate on the caller's data
+// (isweno_batch_autotune).
 #include "batch_kernels.hpp"
 
 #include <algorithm>
@@ -25,20 +28,40 @@ __global__ __launch_bounds__(256) void batch_dt_kernel(const double* U, int64_t 
                                                        const double* dx, double cfl,
                                                        double dt_max, double* dt,
                                                        const int32_t* pstatus,
-                                                       int32_t* active) {
+                                                       int32_t* active, int tc,
+                                                       const int64_t* first, double* halo) {
   const int p = blockIdx.x;
   const int act = pstatus[p] == ST_OK;
   if (threadIdx.x == 0) active[p] = act;
-  if (!act || !(cfl > 0.0)) return;
-  const int64_t lo = offsets[p], hi = offsets[p + 1];
+  if (!act || !(cfl > 0.0 || halo)) return;
+  const int64_t lo = offsets[p], n = offsets[p + 1] - lo;
   double m = 0.0;
-  for (int64_t c = lo + threadIdx.x; c < hi; c += blockDim.x) {
-    double q[5];
-    cell_prim<1>(U, total, c, q);
+  for (int64_t l = threadIdx.x; l < n; l += blockDim.x) {
+    double u[5], q[5];
+#pragma unroll
+    for (int k = 0; k < 5; k++) u[k] = U[k * total + lo + l];
+    if (halo) {
+      // copies of the cells next to the ends of tiles of tc cells, for the
+      // tiles on the other side: [tile][kHalo before it, kHalo after it][5]
+      const int64_t t = n >> 31 ? l / tc : (int64_t)((unsigned)l / (unsigned)tc);
+      const int pos = (int)(l - t * tc);
+      if (pos < kHalo && t > 0) {
+        double* d = halo + ((first[p] + t - 1) * 2 * kHalo + kHalo + pos) * 5;
+#pragma unroll
+        for (int k = 0; k < 5; k++) d[k] = u[k];
+      }
+      if (pos >= tc - kHalo && (t + 1) * tc < n) {
+        double* d = halo + ((first[p] + t + 1) * 2 * kHalo + pos - (tc - kHalo)) * 5;
+#pragma unroll
+        for (int k = 0; k < 5; k++) d[k] = u[k];
+      }
+    }
+    cons_prim<1>(u, q);
     const double cs = sqrt(sound2<double>(q[0], q[2], q[3], q[4]));
     const double s = (fabs(q[1]) + cs) / dx[p];
     m = (s > m || s != s) ? s : m;
   }
+  if (!(cfl > 0.0)) return;
   __shared__ double red[256];
   red[threadIdx.x] = m;
   __syncthreads();
@@ -62,6 +85,11 @@ static hipError_t launch_batch_stage(int precision, int tl, const BatchArgs& a, 
                                   : launch_stage_t<double>(tl, a, mode, blocks, s);
 }
 
+static hipError_t launch_batch_step(int precision, int nthr, const BatchArgs& a, hipStream_t s) {
+  return precision == ISWENO_FP32 ? launch_batch_step_f32(nthr, a, s)
+                                  : launch_step_t<double>(nthr, a, s);
+}
+
 }  // namespace isw
 
 // ---------------------------------------------------------------------------
@@ -74,6 +102,8 @@ struct TileTable {
   int64_t* start = nullptr;
   int32_t* prob = nullptr;
   int64_t ntiles = 0;
+  int64_t* first = nullptr;  // whole steps: first tile of each problem
+  double* halo = nullptr;    // whole steps: the cells next to every tile's ends
 };
 
 struct isweno_batch_plan {
@@ -84,10 +114,10 @@ struct isweno_batch_plan {
   int32_t bc_lo = 0, bc_hi = 0;
   int64_t* offsets = nullptr;  // device
   double* dx = nullptr;        // device
-  double* ws = nullptr;        // U1, U2 (device, 2 x 5 x total)
+  double* ws = nullptr;        // U1, U2 (device, 2 x 5 x total; stage launches only)
   int32_t* active = nullptr;   // per problem, written at the start of each step
   int32_t* tune_status = nullptr;  // per problem, for the autotuner's scratch runs
-  std::map<int, TileTable> tables;  // by tile length
+  std::map<int, TileTable> tables;  // by lanes per workgroup - 1
   int tl = 255;
   int blocks_per_cu = 4;
   hipStream_t cap = nullptr;   // capture stream
@@ -103,11 +133,29 @@ static void free_graphs(isweno_batch_plan* p) {
   p->graphs.clear();
 }
 
-static int build_table(isweno_batch_plan* p, int tl) {
-  if (p->tables.count(tl)) return ISWENO_OK;
-  std::vector<int64_t> st;
+// Whole steps in one launch: every plan but those with a periodic end.
+static bool whole_steps(const isweno_batch_plan* p) {
+  return p->bc_lo != ISWENO_BC_PERIODIC && p->bc_hi != ISWENO_BC_PERIODIC;
+}
+
+static void free_table(TileTable& t) {
+  (void)hipFree(t.start);
+  (void)hipFree(t.prob);
+  (void)hipFree(t.first);
+  (void)hipFree(t.halo);
+  t = TileTable{};
+}
+
+// The tile list for a workgroup of tl + 1 lanes: tiles of tl cells per stage
+// launch, or of step_tile(tl + 1) cells for whole steps.
+static int build_table(isweno_batch_plan* p, int key) {
+  if (p->tables.count(key)) return ISWENO_OK;
+  const bool whole = whole_steps(p);
+  const int tl = whole ? isw::step_tile(key + 1) : key;
+  std::vector<int64_t> st, first;
   std::vector<int32_t> pr;
   for (int32_t q = 0; q < p->nprob; q++) {
+    first.push_back((int64_t)st.size());
     for (int64_t c = p->host_offsets[q]; c < p->host_offsets[q + 1]; c += tl) {
       st.push_back(c);
       pr.push_back(q);
@@ -115,17 +163,20 @@ static int build_table(isweno_batch_plan* p, int tl) {
   }
   TileTable t;
   t.ntiles = (int64_t)st.size();
-  if (hipMalloc(&t.start, st.size() * sizeof(int64_t)) != hipSuccess) return ISWENO_ERR_DEVICE;
-  if (hipMalloc(&t.prob, pr.size() * sizeof(int32_t)) != hipSuccess) {
-    (void)hipFree(t.start);
+  auto put = [](auto** d, const auto& v) {
+    const size_t bytes = v.size() * sizeof(v[0]);
+    return hipMalloc(d, bytes) == hipSuccess &&
+           hipMemcpy(*d, v.data(), bytes, hipMemcpyHostToDevice) == hipSuccess;
+  };
+  bool ok = put(&t.start, st) && put(&t.prob, pr);
+  if (ok && whole)
+    ok = put(&t.first, first) &&
+         hipMalloc(&t.halo, sizeof(double) * 5 * 2 * isw::kHalo * st.size()) == hipSuccess;
+  if (!ok) {
+    free_table(t);
     return ISWENO_ERR_DEVICE;
   }
-  if (hipMemcpy(t.start, st.data(), st.size() * sizeof(int64_t), hipMemcpyHostToDevice) !=
-          hipSuccess ||
-      hipMemcpy(t.prob, pr.data(), pr.size() * sizeof(int32_t), hipMemcpyHostToDevice) !=
-          hipSuccess)
-    return ISWENO_ERR_DEVICE;
-  p->tables[tl] = t;
+  p->tables[key] = t;
   return ISWENO_OK;
 }
 
@@ -143,12 +194,10 @@ static hipError_t enqueue_step(isweno_batch_plan* p, const isweno_opts* o, doubl
                                isweno_stats* stats, int32_t* pstatus, int tl, int bpc,
                                hipStream_t s) {
   const TileTable& t = p->tables[tl];
-  const int64_t sz = 5 * p->total;
-  double* U1 = p->ws;
-  double* U2 = p->ws + sz;
   {
     hipLaunchKernelGGL(isw::batch_dt_kernel, dim3(p->nprob), dim3(256), 0, s, U, p->total,
-                       p->offsets, p->dx, o->cfl, o->dt_max, dt, pstatus, p->active);
+                       p->offsets, p->dx, o->cfl, o->dt_max, dt, pstatus, p->active,
+                       isw::step_tile(tl + 1), t.first, t.halo);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
@@ -168,11 +217,18 @@ static hipError_t enqueue_step(isweno_batch_plan* p, const isweno_opts* o, doubl
   a.weights = o->weights;
   a.mood = o->mood;
   a.eps = o->eps;
+  if (whole_steps(p)) {
+    a.U = U;
+    a.halo = t.halo;
+    return isw::launch_batch_step(o->precision, tl + 1, a, s);
+  }
   a.U0 = U;
   int64_t blocks64 = (int64_t)p->ncu * bpc;
   if (blocks64 > t.ntiles) blocks64 = t.ntiles;
   if (blocks64 < 1) blocks64 = 1;
   const int blocks = (int)blocks64;
+  double* U1 = p->ws;
+  double* U2 = p->ws + 5 * p->total;
   hipError_t e;
   a.Uin = U;
   a.Uout = U1;
@@ -216,7 +272,8 @@ int isweno_batch_plan_create(isweno_ctx* ctx, int32_t nprob, const int64_t* offs
   p->host_offsets.assign(offsets, offsets + nprob + 1);
   bool ok = hipMalloc(&p->offsets, sizeof(int64_t) * (nprob + 1)) == hipSuccess &&
             hipMalloc(&p->dx, sizeof(double) * nprob) == hipSuccess &&
-            hipMalloc(&p->ws, sizeof(double) * 10 * p->total) == hipSuccess &&
+            (whole_steps(p) ||
+             hipMalloc(&p->ws, sizeof(double) * 10 * p->total) == hipSuccess) &&
             hipMalloc(&p->active, sizeof(int32_t) * nprob) == hipSuccess &&
             hipMalloc(&p->tune_status, sizeof(int32_t) * nprob) == hipSuccess &&
             hipMemcpy(p->offsets, offsets, sizeof(int64_t) * (nprob + 1),
@@ -237,10 +294,7 @@ void isweno_batch_plan_destroy(isweno_batch_plan* p) {
   (void)hipSetDevice(p->device);
   (void)hipDeviceSynchronize();
   free_graphs(p);
-  for (auto& kv : p->tables) {
-    (void)hipFree(kv.second.start);
-    (void)hipFree(kv.second.prob);
-  }
+  for (auto& kv : p->tables) free_table(kv.second);
   if (p->offsets) (void)hipFree(p->offsets);
   if (p->dx) (void)hipFree(p->dx);
   if (p->ws) (void)hipFree(p->ws);
@@ -276,6 +330,7 @@ int isweno_batch_autotune(isweno_ctx* ctx, isweno_batch_plan* p, const isweno_op
   for (int tl : kTiles) {
     if ((r = build_table(p, tl)) != ISWENO_OK) break;
     for (int bpc : kBlocksPerCU) {
+      if (whole_steps(p) && bpc != kBlocksPerCU[0]) continue;  // one workgroup per tile
       float ms_min = 1e30f;
       for (int rep = 0; rep < 3 && r == ISWENO_OK; rep++) {
         if (hipMemcpyAsync(S, U, bytes, hipMemcpyDeviceToDevice, s) != hipSuccess ||

@@ -11,4 +11,8 @@ hipError_t launch_batch_stage_f32(int tl, const BatchArgs& a, int mode, int bloc
   return launch_stage_t<float>(tl, a, mode, blocks, s);
 }
 
+hipError_t launch_batch_step_f32(int nthr, const BatchArgs& a, hipStream_t s) {
+  return launch_step_t<float>(nthr, a, s);
+}
+
 }  // namespace isw

@@ -282,9 +282,15 @@ __device__ __forceinline__ bool latched(const StatsDev* stats) {
 // (where some cell of the wave differs in its density the others are not
 // compared: a tile needs one difference) and TILE_FLUIDS.
 template <int N>
+__device__ __forceinline__ bool other_fluid(const double* u, const double* ref) {
+  return (__double_as_longlong(u[N - 2]) != __double_as_longlong(ref[N - 2])) |
+         (__double_as_longlong(u[N - 1]) != __double_as_longlong(ref[N - 1]));
+}
+
+template <int N>
 __device__ __forceinline__ int differs(const double* u, const double* ref, bool flip) {
   auto ne = [&](int c) { return __double_as_longlong(u[c]) != __double_as_longlong(ref[c]); };
-  const bool f = ne(N - 2) | ne(N - 1);
+  const bool f = other_fluid<N>(u, ref);
   bool d = flip | f | ne(0);
   if (!__any(d)) {
 #pragma unroll
