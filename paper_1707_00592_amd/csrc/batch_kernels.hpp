@@ -86,7 +86,7 @@ __global__ __launch_bounds__(TL + 1, sizeof(T) == 4 ? 6 : 1) void batch_stage_ke
       double u[NC], q[NC];
 #pragma unroll
       for (int c = 0; c < NC; c++) u[c] = g.Uin[c * total + lo + li];
-      found |= differs<NC>(u, ref, flip);
+      found |= differs<NC, sizeof(T) == 8>(u, ref, flip);
       cons_prim<1, T>(u, q);
       const bool inr = sizeof(T) == 8 && in_range<1>(q);
       if constexpr (sizeof(T) == 8) found |= inr ? 0 : TILE_FAR;
@@ -147,17 +147,22 @@ __global__ __launch_bounds__(TL + 1, sizeof(T) == 4 ? 6 : 1) void batch_stage_ke
       sf[NC * NF + j] = T(us);
     }
     __syncthreads();
-    const Div64<T> bydx(g.dx[prob]);
+    const CellSize<T> dx(g.dx[prob]);
     for (int j = tid; j < len; j += NTHR) {
       const int64_t cell = lo + l0 + j;
+      double x[NC + 2];
 #pragma unroll
       for (int k = 0; k < NC; k++) {
-        double r = bydx(-(double(sf[k * NF + j + 1]) - double(sf[k * NF + j])));
+        x[k] = -(double(sf[k * NF + j + 1]) - double(sf[k * NF + j]));
         if (k >= 3)
-          r = r + bydx(double(sq[k * NP + j + 3]) *
-                       (double(sf[NC * NF + j + 1]) - double(sf[NC * NF + j])));
-        put(k * total + cell, r, [&](int64_t o) { return g.Uin[o]; });
+          x[k + 2] = double(sq[k * NP + j + 3]) *
+                     (double(sf[NC * NF + j + 1]) - double(sf[NC * NF + j]));
       }
+      dx.template quotients<NC + 2>(x);
+#pragma unroll
+      for (int k = 0; k < NC; k++)
+        put(k * total + cell, k >= 3 ? x[k] + x[k + 2] : x[k],
+            [&](int64_t o) { return g.Uin[o]; });
     }
     __syncthreads();  // LDS is reused by the next tile
   }
@@ -242,13 +247,13 @@ __global__ __launch_bounds__(NTHR, 4) void batch_step_kernel(BatchArgs g) {
       double v[NC], q[NC];
 #pragma unroll
       for (int c = 0; c < NC; c++) v[c] = un(c, r);
-      found |= differs<NC>(v, ref, false);
+      found |= differs<NC, sizeof(T) == 8>(v, ref, false);
       cons_prim<1, T>(v, q);
       if constexpr (sizeof(T) == 8) found |= in_range<1>(q) ? 0 : TILE_FAR;
       stage_cell(r, q);
     }
   }
-  const Div64<T> bydx(g.dx[prob]);
+  const CellSize<T> dx(g.dx[prob]);
   int my3 = 0, my1 = 0;
 #pragma unroll 1
   for (int stage = 0; stage < 3; stage++) {
@@ -264,7 +269,7 @@ __global__ __launch_bounds__(NTHR, 4) void batch_step_kernel(BatchArgs g) {
       const bool inr = sizeof(T) == 8 && in_range<1>(q);
       // (a stage's rounding moves Gamma and Pi also within one fluid: looked at
       // in every stage)
-      if (stage == 0) found |= differs<NC>(u, ref, false);
+      if (stage == 0) found |= differs<NC, sizeof(T) == 8>(u, ref, false);
       else if constexpr (sizeof(T) == 8) found |= other_fluid<NC>(u, ref) ? TILE_FLUIDS : 0;
       if constexpr (sizeof(T) == 8) found |= inr ? 0 : TILE_FAR;
       if (mine >= 0 && mine < len)
@@ -318,11 +323,18 @@ __global__ __launch_bounds__(NTHR, 4) void batch_step_kernel(BatchArgs g) {
     __syncthreads();
     if (!cell || mine < -m || mine >= len + m) continue;
     const double usr = double(sf[NC * NTHR + tid + 1]);
+    double x[NC + 2];
+#pragma unroll
+    for (int k = 0; k < NC; k++) {
+      x[k] = -(double(sf[k * NTHR + tid + 1]) - F[k]);
+      // (Gamma and Pi are their own primitives)
+      if (k >= 3) x[k + 2] = double(T(su[k * NTHR + tid])) * (usr - us);
+    }
+    dx.template quotients<NC + 2>(x);
 #pragma unroll
     for (int k = 0; k < NC; k++) {
       const double u = su[k * NTHR + tid], u0 = stage == 0 ? u : un(k, mine);
-      double r = bydx(-(double(sf[k * NTHR + tid + 1]) - F[k]));
-      if (k >= 3) r = r + bydx(double(T(u)) * (usr - us));  // Gamma and Pi are their own primitives
+      const double r = k >= 3 ? x[k] + x[k + 2] : x[k];
       if (stage == 0) su[k * NTHR + tid] = u0 + h * r;
       else if (stage == 1) su[k * NTHR + tid] = 0.75 * u0 + 0.25 * (u + h * r);
       else g.U[k * total + lo + l0 + mine] = (1.0 / 3.0) * u0 + (2.0 / 3.0) * (u + h * r);

@@ -143,7 +143,7 @@ __global__ __launch_bounds__(kThreads, CUT && GATHER ? 2 : 4) void stage2d_kerne
     const int64_t cell = iy * nx + ix;
     double u[NC], q[NC];
     input(cell, u);
-    found |= differs<NC>(u, ref, flip);
+    found |= differs<NC, true>(u, ref, flip);
     cons_prim<NDIM, T>(u, q);
     const bool inr = sizeof(T) == 8 && in_range<NDIM>(q);
     if constexpr (sizeof(T) == 8) found |= inr ? 0 : TILE_FAR;
@@ -231,7 +231,6 @@ __global__ __launch_bounds__(kThreads, CUT && GATHER ? 2 : 4) void stage2d_kerne
       return;
     }
   }
-  const Div64<T> bydx(g.dx[0]), bydy(g.dx[1]);
   auto xstencil = [&](int f) {  // x face (f % 16, f / 16)
     LdsStencil2<T> st;
     st.base = &sq[(f / 16 + 3) * SX + f % 16];
@@ -397,25 +396,27 @@ __global__ __launch_bounds__(kThreads, CUT && GATHER ? 2 : 4) void stage2d_kerne
   // component 2, u_t = u component 1), then the output step
   if (mine) {
     const int fb = cy * TX + cx, fa = fb + TX;  // the cell's lower and upper y faces
-    double rx[NC];
+    // numerators: the flux differences and, after them, the sources of Gamma
+    // and Pi
+    double x[NC + 2], y[NC + 2];
 #pragma unroll
     for (int kk = 0; kk < NC; kk++) {
-      double r = bydx(-(Fr[kk] - F[kk]));
+      x[kk] = -(Fr[kk] - F[kk]);
+      y[kk] = -(double(sfy[kk * NFY + fa]) - double(sfy[kk * NFY + fb]));
       if (kk >= 4) {
         const double phi = sq[kk * QROW + (cy + 3) * SX + cx + 3];
-        r = r + bydx(phi * (usr - us));
+        x[kk + 2] = phi * (usr - us);
+        y[kk + 2] = phi * (double(sfy[NC * NFY + fa]) - double(sfy[NC * NFY + fb]));
       }
-      rx[kk] = r;
     }
+    CellSize<T>(g.dx[0]).template quotients<NC + 2>(x);
+    CellSize<T>(g.dx[1]).template quotients<NC + 2>(y);
 #pragma unroll
     for (int kk = 0; kk < NC; kk++) {
       const int kc = axis_comp<NDIM, 1>(kk);
-      double r = bydy(-(double(sfy[kk * NFY + fa]) - double(sfy[kk * NFY + fb])));
-      if (kk >= 4) {
-        const double phi = sq[kc * QROW + (cy + 3) * SX + cx + 3];
-        r = r + bydy(phi * (double(sfy[NC * NFY + fa]) - double(sfy[NC * NFY + fb])));
-      }
-      put(kc, rx[kc] + r, [&](int64_t o) {
+      const double rx = kc >= 4 ? x[kc] + x[kc + 2] : x[kc];
+      const double ry = kk >= 4 ? y[kk] + y[kk + 2] : y[kk];
+      put(kc, rx + ry, [&](int64_t o) {
         if constexpr (FROM_L) return g.U0[o] + h1 * g.R[o];  // as stage 1 would have written it
         else return g.Uin[o];
       });

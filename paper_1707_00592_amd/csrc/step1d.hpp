@@ -66,7 +66,7 @@ __global__ __launch_bounds__(NTHR) void step1d_kernel(Step1dArgs g) {
   } else {
     h = *g.dt;
   }
-  const Div64<T> bydx(g.dx);
+  const CellSize<T> dx(g.dx);
 #pragma unroll 1
   for (int stage = 0; stage < 3; stage++) {
     double q[NC];
@@ -120,10 +120,16 @@ __global__ __launch_bounds__(NTHR) void step1d_kernel(Step1dArgs g) {
     if (g.stats && (notes & TILE_BAD) && stage < 2) return;
     if (!cell) continue;
     const double usr = double(sf[NC * NTHR + tid + 1]);
+    double x[NC + 2];
 #pragma unroll
     for (int k = 0; k < NC; k++) {
-      double r = bydx(-(double(sf[k * NTHR + tid + 1]) - F[k]));
-      if (k >= 3) r = r + bydx(double(T(q[k])) * (usr - us));
+      x[k] = -(double(sf[k * NTHR + tid + 1]) - F[k]);
+      if (k >= 3) x[k + 2] = double(T(q[k])) * (usr - us);
+    }
+    dx.template quotients<NC + 2>(x);
+#pragma unroll
+    for (int k = 0; k < NC; k++) {
+      const double r = k >= 3 ? x[k] + x[k + 2] : x[k];
       if (stage == 0) u[k] = u0[k] + h * r;
       else if (stage == 1) u[k] = 0.75 * u0[k] + 0.25 * (u[k] + h * r);
       else g.U[(int64_t)k * n + tid] = (1.0 / 3.0) * u0[k] + (2.0 / 3.0) * (u[k] + h * r);

@@ -198,7 +198,7 @@ __global__ __launch_bounds__(NTHR, MODE == OUT_PARTIAL_S ? 5 : 1) void sweep_ker
     double u[NC], q[NC];
 #pragma unroll
     for (int c = 0; c < NC; c++) u[c] = g.Uin[c * N + cell];
-    found |= differs<NC>(u, ref, flip);
+    found |= differs<NC, sizeof(T) == 8>(u, ref, flip);
     cons_prim<NDIM, T>(u, q);
     const bool inr = sizeof(T) == 8 && in_range<NDIM>(q);
     if constexpr (sizeof(T) == 8) found |= inr ? 0 : TILE_FAR;
@@ -237,7 +237,9 @@ __global__ __launch_bounds__(NTHR, MODE == OUT_PARTIAL_S ? 5 : 1) void sweep_ker
 
   // 2. faces: thread tid owns face (w, j); with ALIAS the values wait in
   // registers until every face has read sq
-  const TileState tile{!(notes & TILE_FAR) && eps_in_range(g.eps), !(notes & TILE_FLUIDS)};
+  // (one_fluid not in the float form: its registers cost the eighth wave)
+  const TileState tile{!(notes & TILE_FAR) && eps_in_range(g.eps),
+                       sizeof(T) == 8 && !(notes & TILE_FLUIDS)};
   int my3 = 0, my1 = 0, mys = 0;
   // FP64 x tiles of 8 rows x 32 faces: each wave takes an 8 x 8 block, so a
   // front across x splits fewer waves between the linear-weight form and
@@ -296,7 +298,7 @@ __global__ __launch_bounds__(NTHR, MODE == OUT_PARTIAL_S ? 5 : 1) void sweep_ker
   __syncthreads();
 
   // 3. cells
-  const Div64<T> bydx(g.dx[D]);
+  const CellSize<T> dx(g.dx[D]);
   for (int e = tid; e < TW * TL; e += NTHR) {
     const int w = D == 0 ? e / TL : e % TW;
     const int j = D == 0 ? e % TL : e / TW;
@@ -304,16 +306,23 @@ __global__ __launch_bounds__(NTHR, MODE == OUT_PARTIAL_S ? 5 : 1) void sweep_ker
     const int64_t l = l0 + j;
     if (a >= geo.nA || l >= geo.nL) continue;
     const int64_t cell = a * geo.sA + l * geo.sL + tt * geo.sT;
+    // numerators: the flux differences and, after them, the sources of Gamma
+    // and Pi
+    double x[NC + 2];
 #pragma unroll
     for (int k = 0; k < NC; k++) {
-      const int kc = axis_comp<NDIM, D>(k);
-      double r = bydx(-(double(sf[fidx(k, w, j + 1)]) - double(sf[fidx(k, w, j)])));
-      if (k >= 3 + (NDIM - 1)) {
-        const double phi = sq[lidx(kc, w, j + 3)];
-        r = r + bydx(phi * (double(sf[fidx(NC, w, j + 1)]) - double(sf[fidx(NC, w, j)])));
+      x[k] = -(double(sf[fidx(k, w, j + 1)]) - double(sf[fidx(k, w, j)]));
+      if (k >= NC - 2) {
+        const double phi = sq[lidx(k, w, j + 3)];
+        x[k + 2] = phi * (double(sf[fidx(NC, w, j + 1)]) - double(sf[fidx(NC, w, j)]));
       }
-      sweep_put<MODE, READ_R>(g, kc * N + cell, r, [&](int64_t o) { return g.Uin[o]; });
     }
+    dx.template quotients<NC + 2>(x);
+#pragma unroll
+    for (int k = 0; k < NC; k++)
+      sweep_put<MODE, READ_R>(g, axis_comp<NDIM, D>(k) * N + cell,
+                              k >= NC - 2 ? x[k] + x[k + 2] : x[k],
+                              [&](int64_t o) { return g.Uin[o]; });
   }
 }
 
@@ -371,7 +380,7 @@ __global__ __launch_bounds__(NTHR) void sweep_mlp_kernel(SweepArgs g) {
     double u[NC], q[NC];
 #pragma unroll
     for (int c = 0; c < NC; c++) u[c] = g.Uin[c * N + cell];
-    found |= differs<NC>(u, ref, flip);
+    found |= differs<NC, true>(u, ref, flip);
     cons_prim<NDIM, T>(u, q);
     if (p >= 3 && p < 3 + TL && l < geo.nL) found |= cell_ok_u<NDIM>(u, q) ? 0 : TILE_BAD;
     if (flip) q[1 + D] = -q[1 + D];
@@ -439,7 +448,7 @@ __global__ __launch_bounds__(NTHR) void sweep_mlp_kernel(SweepArgs g) {
   __syncthreads();
 
   // 3. cells
-  const Div64<T> bydx(g.dx[D]);
+  const CellSize<T> dx(g.dx[D]);
   for (int e = tid; e < TW * TL; e += NTHR) {
     const int w = D == 0 ? e / TL : e % TW;
     const int j = D == 0 ? e % TL : e / TW;
@@ -447,16 +456,23 @@ __global__ __launch_bounds__(NTHR) void sweep_mlp_kernel(SweepArgs g) {
     const int64_t l = l0 + j;
     if (a >= geo.nA || l >= geo.nL) continue;
     const int64_t cell = a * geo.sA + l * geo.sL + tt * geo.sT;
+    // numerators: the flux differences and, after them, the sources of Gamma
+    // and Pi
+    double x[NC + 2];
 #pragma unroll
     for (int k = 0; k < NC; k++) {
-      const int kc = axis_comp<NDIM, D>(k);
-      double r = bydx(-(double(sf[fidx(k, w, j + 1)]) - double(sf[fidx(k, w, j)])));
-      if (k >= 3 + (NDIM - 1)) {
-        const double phi = sq[lidx(kc, w, j + 3)];
-        r = r + bydx(phi * (double(sf[fidx(NC, w, j + 1)]) - double(sf[fidx(NC, w, j)])));
+      x[k] = -(double(sf[fidx(k, w, j + 1)]) - double(sf[fidx(k, w, j)]));
+      if (k >= NC - 2) {
+        const double phi = sq[lidx(k, w, j + 3)];
+        x[k + 2] = phi * (double(sf[fidx(NC, w, j + 1)]) - double(sf[fidx(NC, w, j)]));
       }
-      sweep_put<MODE, READ_R>(g, kc * N + cell, r, [&](int64_t o) { return g.Uin[o]; });
     }
+    dx.template quotients<NC + 2>(x);
+#pragma unroll
+    for (int k = 0; k < NC; k++)
+      sweep_put<MODE, READ_R>(g, axis_comp<NDIM, D>(k) * N + cell,
+                              k >= NC - 2 ? x[k] + x[k + 2] : x[k],
+                              [&](int64_t o) { return g.Uin[o]; });
   }
 }
 
