@@ -73,13 +73,26 @@ __device__ __forceinline__ int wave_sum(int v) {
   return v;
 }
 
-// Boundary map of a ghost/interior position l (-3..n+2) on a line of n
-// cells: interior index and whether the normal velocity is mirrored.
+// A value the compiler may not reason about (no instruction).
+__device__ __forceinline__ void opaque(int64_t& v) { asm("" : "+v"(v)); }
+
+// Boundary map of a ghost/interior position l, a few cells at most outside
+// the line of n cells (-3..n+2): interior index and whether the normal
+// velocity is mirrored.  A periodic position is brought back by adding lines
+// (one, unless the line is shorter than the halo): the 64-bit remainders that
+// stood here are about 150 instructions each in every tile at an end, and
+// the compiler makes one of a plain loop again (opaque).
 __device__ __forceinline__ int64_t bc_index(int64_t l, int64_t n, int bclo,
                                             int bchi, bool& flip) {
   flip = false;
   if (l < 0) {
-    if (bclo == 1) return ((l % n) + n) % n;
+    if (bclo == 1) {
+      do {
+        l += n;
+        opaque(l);
+      } while (l < 0);
+      return l;
+    }
     if (bclo == 2) {
       flip = true;
       return -l - 1;
@@ -87,7 +100,13 @@ __device__ __forceinline__ int64_t bc_index(int64_t l, int64_t n, int bclo,
     return 0;
   }
   if (l >= n) {
-    if (bchi == 1) return l % n;
+    if (bchi == 1) {
+      do {
+        l -= n;
+        opaque(l);
+      } while (l >= n);
+      return l;
+    }
     if (bchi == 2) {
       flip = true;
       return 2 * n - 1 - l;
@@ -95,6 +114,14 @@ __device__ __forceinline__ int64_t bc_index(int64_t l, int64_t n, int bclo,
     return n - 1;
   }
   return l;
+}
+
+// k s for 0 <= k < 2^24 and a stride 0 <= s < 2^56: one wide multiply-add
+// and a 24-bit one.  The general 64-bit product has three multiplies at a
+// quarter of the rate, and every staged cell and every output cell paid it.
+__device__ __forceinline__ int64_t times_stride(int k, int64_t s, int64_t plus) {
+  const uint64_t lo = (uint64_t)(uint32_t)k * (uint32_t)s + (uint64_t)plus;
+  return (int64_t)(lo + ((uint64_t)__umul24((unsigned)k, (unsigned)((uint64_t)s >> 32)) << 32));
 }
 
 // FP64 quotients in the kernels: exact (IEEE) in the FP64 form, which
