@@ -9,7 +9,8 @@
 
 namespace isw {
 
-constexpr int MLP_WAVES = 4;  // waves per workgroup in the training kernels
+constexpr int MLP_WAVES = 4;   // waves per workgroup of the forward kernel
+constexpr int GRAD_WAVES = 8;  // and of the gradient (one workgroup a CU at 65 536 samples)
 
 // Scale of the value error in the loss and tolerance of the confidence
 // label, in units of the stencil's range (the inputs are normalised to it).
@@ -25,159 +26,247 @@ __device__ __forceinline__ void candidates(float a, float b, float c, float d, f
   q[3] = (1.0f / 3.0f) * a - (7.0f / 6.0f) * b + (11.0f / 6.0f) * c;
 }
 
-// Per-sample loss (unscaled) and logit gradient (scaled by 1/n).  Per side
-// h: qhat_h = sum_k softmax(z_h)_k c_hk, q_h = sum_k y_hk c_hk with c_hk the
-// candidates on the normalised stencil x (left from x0..x4, right from the
-// mirror x5..x1); loss ((qhat_h - q_h) / kValueScale)^2.  Plus binary
-// cross-entropy of the confidence logit against c; c < 0 asks for the
-// label to be formed here: 1 when both |qhat_h - q_h| < kConfTol, else 0.
-__device__ __forceinline__ float sample_loss(const float* z, const float* y, const float* x,
-                                             float c, float inv_n, float* dz) {
-  float loss = 0.0f, err = 0.0f;
+// One side of a sample: qhat = sum_k softmax(z)_k c_k, q = sum_k y_k c_k with
+// c_k the candidates on the side's normalised stencil x (x0..x4 on the left,
+// the mirror x5..x1 on the right); r = (qhat - q) / kValueScale, whose square
+// is the side's loss, and dz the gradient of the loss to its logits, scaled
+// by 1/n.  Returns |qhat - q|.
+__device__ __forceinline__ float side_loss(const float* z, const float* y, const float* x,
+                                           float inv_n, float& r, float* dz) {
+  float cand[4];
+  candidates(x[0], x[1], x[2], x[3], x[4], cand);
+  float m = z[0];
 #pragma unroll
-  for (int h = 0; h < 2; h++) {
-    const float* zh = z + 4 * h;
-    float cand[4];
-    if (h == 0)
-      candidates(x[0], x[1], x[2], x[3], x[4], cand);
-    else
-      candidates(x[5], x[4], x[3], x[2], x[1], cand);
-    float m = zh[0];
+  for (int k = 1; k < 4; k++) m = fmaxf(m, z[k]);
+  float e[4], s = 0.0f;
 #pragma unroll
-    for (int k = 1; k < 4; k++) m = fmaxf(m, zh[k]);
-    float e[4], s = 0.0f;
-#pragma unroll
-    for (int k = 0; k < 4; k++) {
-      e[k] = __expf(zh[k] - m);
-      s += e[k];
-    }
-    float qh = 0.0f, qt = 0.0f;
-#pragma unroll
-    for (int k = 0; k < 4; k++) {
-      e[k] = e[k] / s;
-      qh += e[k] * cand[k];
-      qt += y[4 * h + k] * cand[k];
-    }
-    const float r = (qh - qt) * (1.0f / kValueScale);
-    loss += r * r;
-    err = fmaxf(err, fabsf(qh - qt));
-    const float g = 2.0f * r * (1.0f / kValueScale) * inv_n;
-#pragma unroll
-    for (int k = 0; k < 4; k++) dz[4 * h + k] = g * e[k] * (cand[k] - qh);
+  for (int k = 0; k < 4; k++) {
+    e[k] = __expf(z[k] - m);
+    s += e[k];
   }
-  if (c < 0.0f) c = err < kConfTol ? 1.0f : 0.0f;
-  const float zc = z[8];
-  const float sig = 1.0f / (1.0f + __expf(-zc));
-  loss += fmaxf(zc, 0.0f) - zc * c + log1pf(__expf(-fabsf(zc)));
-  dz[8] = (sig - c) * inv_n;
-  return loss;
+  float qh = 0.0f, qt = 0.0f;
+#pragma unroll
+  for (int k = 0; k < 4; k++) {
+    e[k] = e[k] / s;
+    qh += e[k] * cand[k];
+    qt += y[k] * cand[k];
+  }
+  r = (qh - qt) * (1.0f / kValueScale);
+  const float g = 2.0f * r * (1.0f / kValueScale) * inv_n;
+#pragma unroll
+  for (int k = 0; k < 4; k++) dz[k] = g * e[k] * (cand[k] - qh);
+  return fabsf(qh - qt);
+}
+
+// One wave's exchange between the layers and the weight gradients, rows of 32
+// samples (a row's stride spreads 32 rows over all banks, for 4 bf16 and for
+// 4 floats a lane): activations and the gradient of one layer at a time.
+constexpr int kSampleRow = 36;
+struct alignas(16) GradTile {
+  uint16_t h1[MLP_H * kSampleRow], h2[MLP_H * kSampleRow], x[MLP_NI * kSampleRow];
+  float d[MLP_H * kSampleRow];
+};
+
+// Orders a wave's own LDS writes and reads for the compiler (the hardware
+// runs them in order).
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// Four floats from any address of a float.
+struct __attribute__((packed, aligned(4))) Float4u {
+  float v[4];
+};
+__device__ __forceinline__ bf16x4 load_bf16x4(const float* p) {
+  const Float4u f = *reinterpret_cast<const Float4u*>(p);
+  return pack_bf16x4(f.v[0], f.v[1], f.v[2], f.v[3]);
+}
+
+// G += d a^T over the tile's samples (d: rows of T.d below `rows`, zero above;
+// a: rows of `act` below `arows`), and the sum of d's row l % 32 over the
+// samples (the bias gradient) as the return value.
+__device__ __forceinline__ float grad_outer(const GradTile& T, const uint16_t* act, int rows,
+                                            int arows, f32x16& G) {
+  const int l = threadIdx.x & 63, i = l & 31, kh = (l >> 5) * 4;
+  float sum = 0.0f;
+#pragma unroll
+  for (int q = 0; q < 4; q++) {
+    float4 d = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    bf16x4 a = {0, 0, 0, 0};
+    if (i < rows) d = *reinterpret_cast<const float4*>(&T.d[i * kSampleRow + 8 * q + kh]);
+    if (i < arows) a = *reinterpret_cast<const bf16x4*>(&act[i * kSampleRow + 8 * q + kh]);
+    sum = ((sum + d.x) + d.y + d.z) + d.w;
+    G = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(pack_bf16x4(d.x, d.y, d.z, d.w), a, G, 0, 0, 0);
+  }
+  return sum + __shfl_xor(sum, 32);
 }
 
 // Forward + backward over n samples; each workgroup writes its partial
 // gradient (and loss) to part[blockIdx.x][MLP_NPARAM + 1].
-__global__ __launch_bounds__(64 * MLP_WAVES) void mlp_grad_kernel(
+//
+// A wave has one tile of 32 samples at 65 536 samples, so the kernel is one
+// tile's chain of seven products long, with the exchange between them.  The
+// layers run transposed, h^T = W x^T (see the inference in mlp.hpp): a
+// layer's accumulators are the next product's operand in both directions, the
+// weights come straight from the parameters (rows as 4 floats a lane, columns
+// coalesced), and each half of the wave forms one side of the sample's loss.
+// Only the weight gradients, whose contraction is over the samples, go
+// through LDS, with 8- and 16-byte reads free of bank conflicts.  Before, all
+// operands were 2-byte LDS reads of rows 64 bytes apart (8 lanes a bank) and
+// half the lanes idled in the loss: 24 us at 65 536 samples; now 15.2 us with
+// 4 waves a workgroup and 10.3 us with 8 (half the partial rows to write).
+// Masters, biases, loss, gradients and every sum are float; operands of the
+// products are rounded to bf16.
+//
+// The loss of a sample: the squares of side_loss's two r, and binary
+// cross-entropy of the confidence logit against c; c < 0 asks for the label
+// to be formed here: 1 when both |qhat - q| < kConfTol, else 0.
+__global__ __launch_bounds__(64 * GRAD_WAVES) void mlp_grad_kernel(
     const float* __restrict__ P, const float* __restrict__ X, const float* __restrict__ Y,
     const float* __restrict__ Cc, int64_t n, float* __restrict__ part) {
-  __shared__ MlpLds W;
-  __shared__ MlpTile tiles[MLP_WAVES];
-  __shared__ uint16_t dzb[MLP_WAVES][32 * 16];   // dz (bf16), 16 columns (9 used)
-  __shared__ uint16_t dh2[MLP_WAVES][32 * MLP_H];
-  __shared__ uint16_t dh1[MLP_WAVES][32 * MLP_H];
-  __shared__ float red[MLP_WAVES][MLP_NPARAM + 1];
+  // after its last tile a wave's results take the place of its tile
+  __shared__ GradTile tiles[GRAD_WAVES];
+  static_assert(sizeof(GradTile) >= sizeof(float) * (MLP_NPARAM + 1), "results fit the tile");
   const int tid = threadIdx.x, wave = tid >> 6, l = tid & 63;
-  mlp_stage_f32(W, P, tid, blockDim.x);
-  __syncthreads();
-  MlpTile& T = tiles[wave];
+  const int i = l & 31, half = l >> 5, kh = half * 4;
+  GradTile& T = tiles[wave];
   const float inv_n = 1.0f / (float)n;
+  // operands of the forward products (rows of W) and of the backward ones
+  // (columns), and the biases of the lane's accumulator rows
+  bf16x4 w1 = load_bf16x4(P + P_W1 + i * MLP_NI + kh), w2[4], w3[4], w2t[4], w3t[2];
+  float b1[16], b2[16], b3[4];
+#pragma unroll
+  for (int q = 0; q < 4; q++) {
+    w2[q] = load_bf16x4(P + P_W2 + i * MLP_H + 8 * q + kh);
+    w3[q] = bf16x4{0, 0, 0, 0};
+    if (i < MLP_NO) w3[q] = load_bf16x4(P + P_W3 + i * MLP_H + 8 * q + kh);
+    const float* c2 = P + P_W2 + (8 * q + kh) * MLP_H + i;
+    w2t[q] = pack_bf16x4(c2[0], c2[MLP_H], c2[2 * MLP_H], c2[3 * MLP_H]);
+#pragma unroll
+    for (int t = 0; t < 4; t++) {
+      b1[4 * q + t] = P[P_B1 + 8 * q + kh + t];
+      b2[4 * q + t] = P[P_B2 + 8 * q + kh + t];
+    }
+    b3[q] = P[P_B3 + kh + q];
+  }
+  const float* c3 = P + P_W3 + kh * MLP_H + i;
+  w3t[0] = pack_bf16x4(c3[0], c3[MLP_H], c3[2 * MLP_H], c3[3 * MLP_H]);
+  w3t[1] = pack_bf16x4(half == 0 ? P[P_W3 + 8 * MLP_H + i] : 0.0f, 0.0f, 0.0f, 0.0f);
+  const float b3c = P[P_B3 + 8];
+
   f32x16 g1 = zero16(), g2 = zero16(), g3 = zero16();
   float gb1 = 0.0f, gb2 = 0.0f, gb3 = 0.0f, loss = 0.0f;
   const int64_t ntile = (n + 31) / 32;
-  for (int64_t t = (int64_t)blockIdx.x * MLP_WAVES + wave; t < ntile;
-       t += (int64_t)gridDim.x * MLP_WAVES) {
-    const int64_t s0 = t * 32;
-    for (int e = l; e < 32 * MLP_NI; e += 64) {
-      const int64_t s = s0 + e / MLP_NI;
-      T.x[e] = f2bf(s < n ? X[s * MLP_NI + e % MLP_NI] : 0.0f);
+  for (int64_t t0 = (int64_t)blockIdx.x * GRAD_WAVES + wave; t0 < ntile;
+       t0 += (int64_t)gridDim.x * GRAD_WAVES) {
+    const int64_t s = t0 * 32 + i;
+    const bool valid = s < n;
+    Float4u xl = {}, xr = {}, y = {};
+    float c = 0.0f;
+    if (valid) {
+      xl = *reinterpret_cast<const Float4u*>(X + s * MLP_NI);
+      xr = *reinterpret_cast<const Float4u*>(X + s * MLP_NI + 4);
+      y = *reinterpret_cast<const Float4u*>(Y + s * 8 + kh);
+      c = Cc ? Cc[s] : -1.0f;
     }
-    __builtin_amdgcn_s_waitcnt(0);
-    __builtin_amdgcn_wave_barrier();
-    mlp_tile_forward(W, T);
-    // loss and dz: lanes 0..31 own one sample each
-    if (l < 32) {
-      const int64_t s = s0 + l;
-      float dz[9];
-      if (s < n) {
-        float z[9], y[8], xs[MLP_NI];
+    // forward; the lane's rows of each layer are 8 q + kh + t, its column
+    // sample i
+    const bf16x4 xb = half ? pack_bf16x4(xr.v[0], xr.v[1], xr.v[2], xr.v[3])
+                           : pack_bf16x4(xl.v[0], xl.v[1], xl.v[2], xl.v[3]);
 #pragma unroll
-        for (int k = 0; k < 9; k++) z[k] = T.z[l * 16 + k];
+    for (int t = 0; t < 4; t++) T.x[(kh + t) * kSampleRow + i] = (uint16_t)xb[t];
+    auto activate = [&](const f32x16& acc, const float* b, uint16_t* row, bf16x4* h) {
 #pragma unroll
-        for (int k = 0; k < 8; k++) y[k] = Y[s * 8 + k];
+      for (int q = 0; q < 4; q++) {
+        float v[4];
 #pragma unroll
-        for (int k = 0; k < MLP_NI; k++) xs[k] = X[s * MLP_NI + k];
-        loss += sample_loss(z, y, xs, Cc ? Cc[s] : -1.0f, inv_n, dz) * inv_n;
-      } else {
+        for (int t = 0; t < 4; t++) {
+          v[t] = acc[4 * q + t] + b[4 * q + t];
+          v[t] = v[t] > 0.0f ? v[t] : 0.0f;
+        }
+        h[q] = pack_bf16x4(v[0], v[1], v[2], v[3]);
 #pragma unroll
-        for (int k = 0; k < 9; k++) dz[k] = 0.0f;
+        for (int t = 0; t < 4; t++) row[(8 * q + kh + t) * kSampleRow + i] = (uint16_t)h[q][t];
       }
+    };
+    bf16x4 h1[4], h2[4];
+    f32x16 acc = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(w1, xb, zero16(), 0, 0, 0);
+    activate(acc, b1, T.h1, h1);
+    acc = zero16();
 #pragma unroll
-      for (int k = 0; k < 16; k++) {
-        const float v = k < 9 ? dz[k] : 0.0f;
-        dzb[wave][l * 16 + k] = f2bf(v);
-        T.z[l * 16 + k] = v;  // float dz for the bias gradient
+    for (int q = 0; q < 4; q++)
+      acc = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(w2[q], h1[q], acc, 0, 0, 0);
+    activate(acc, b2, T.h2, h2);
+    acc = zero16();
+#pragma unroll
+    for (int q = 0; q < 4; q++)
+      acc = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(w3[q], h2[q], acc, 0, 0, 0);
+    // loss and dz: lane l holds the logits of side l / 32 of sample i, and the
+    // lower half the confidence's
+    float z[4], dz[4], r;
+#pragma unroll
+    for (int k = 0; k < 4; k++) z[k] = acc[k] + b3[k];
+    const float xs[5] = {half ? xr.v[1] : xl.v[0], half ? xr.v[0] : xl.v[1],
+                         half ? xl.v[3] : xl.v[2], half ? xl.v[2] : xl.v[3],
+                         half ? xl.v[1] : xr.v[0]};
+    float err = side_loss(z, y.v, xs, inv_n, r, dz);
+    err = fmaxf(err, __shfl_xor(err, 32));
+    if (c < 0.0f) c = err < kConfTol ? 1.0f : 0.0f;
+    const float zc = acc[4] + b3c;
+    float dc = (1.0f / (1.0f + __expf(-zc)) - c) * inv_n, ls = r * r;
+    if (half) dc = 0.0f;
+    else ls += fmaxf(zc, 0.0f) - zc * c + log1pf(__expf(-fabsf(zc)));
+    if (valid) {
+      loss += ls * inv_n;
+    } else {
+      dc = 0.0f;
+#pragma unroll
+      for (int k = 0; k < 4; k++) dz[k] = 0.0f;
+    }
+    const bf16x4 dz0 = pack_bf16x4(dz[0], dz[1], dz[2], dz[3]);
+    const bf16x4 dz1 = pack_bf16x4(dc, 0.0f, 0.0f, 0.0f);
+#pragma unroll
+    for (int t = 0; t < 4; t++) {
+      T.d[(kh + t) * kSampleRow + i] = dz[t];
+      T.d[(8 + kh + t) * kSampleRow + i] = t == 0 ? dc : 0.0f;
+    }
+    wave_lds_fence();
+    // gW3[j][k] += sum_s dz[s][j] h2[s][k], gb3[j] += sum_s dz[s][j]
+    gb3 += grad_outer(T, T.h2, 16, MLP_H, g3);
+    wave_lds_fence();
+    // d[k][s] = (sum_j W[j][k] d'[j][s]) * relu'(h)
+    auto through_relu = [&](const f32x16& v, const bf16x4* h, bf16x4* d) {
+#pragma unroll
+      for (int q = 0; q < 4; q++) {
+        float m[4];
+#pragma unroll
+        for (int t = 0; t < 4; t++) {
+          m[t] = bf2f((uint16_t)h[q][t]) > 0.0f ? v[4 * q + t] : 0.0f;
+          T.d[(8 * q + kh + t) * kSampleRow + i] = m[t];
+        }
+        d[q] = pack_bf16x4(m[0], m[1], m[2], m[3]);
       }
-    }
-    __builtin_amdgcn_s_waitcnt(0);
-    __builtin_amdgcn_wave_barrier();
-    // gb3[j] = sum_s dz[s][j]
-    if (l < 9) {
-      float s = 0.0f;
-      for (int i = 0; i < 32; i++) s += T.z[i * 16 + l];
-      gb3 += s;
-    }
-    // gW3[j][k] += sum_s dz[s][j] h2[s][k]
-    g3 = mma32<32>(g3, [&](int i, int s) { return i < 16 ? dzb[wave][s * 16 + i] : (uint16_t)0; },
-                   [&](int s, int k) { return T.h2[s * MLP_H + k]; });
-    // dh2[s][k] = (sum_j dz[s][j] W3[j][k]) * relu'(h2)
-    f32x16 acc = mma32<16>(zero16(), [&](int s, int j) { return dzb[wave][s * 16 + j]; },
-                           [&](int j, int k) { return W.w3[j * MLP_H + k]; });
-    float cs = 0.0f;
-#pragma unroll
-    for (int r = 0; r < 16; r++) {
-      const int s = mrow(l, r), k = mcol(l);
-      const float v = bf2f(T.h2[s * MLP_H + k]) > 0.0f ? acc[r] : 0.0f;
-      cs += v;
-      dh2[wave][s * MLP_H + k] = f2bf(v);
-    }
-    cs += __shfl_xor(cs, 32);
-    if (l < 32) gb2 += cs;
-    __builtin_amdgcn_s_waitcnt(0);
-    __builtin_amdgcn_wave_barrier();
+    };
+    bf16x4 d[4];
+    acc = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(w3t[0], dz0, zero16(), 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(w3t[1], dz1, acc, 0, 0, 0);
+    through_relu(acc, h2, d);
+    wave_lds_fence();
     // gW2[j][k] += sum_s dh2[s][j] h1[s][k]
-    g2 = mma32<32>(g2, [&](int j, int s) { return dh2[wave][s * MLP_H + j]; },
-                   [&](int s, int k) { return T.h1[s * MLP_H + k]; });
-    // dh1[s][k] = (sum_j dh2[s][j] W2[j][k]) * relu'(h1)
-    acc = mma32<32>(zero16(), [&](int s, int j) { return dh2[wave][s * MLP_H + j]; },
-                    [&](int j, int k) { return W.w2[j * MLP_H + k]; });
-    cs = 0.0f;
+    gb2 += grad_outer(T, T.h1, MLP_H, MLP_H, g2);
+    wave_lds_fence();
+    acc = zero16();
 #pragma unroll
-    for (int r = 0; r < 16; r++) {
-      const int s = mrow(l, r), k = mcol(l);
-      const float v = bf2f(T.h1[s * MLP_H + k]) > 0.0f ? acc[r] : 0.0f;
-      cs += v;
-      dh1[wave][s * MLP_H + k] = f2bf(v);
-    }
-    cs += __shfl_xor(cs, 32);
-    if (l < 32) gb1 += cs;
-    __builtin_amdgcn_s_waitcnt(0);
-    __builtin_amdgcn_wave_barrier();
+    for (int q = 0; q < 4; q++)
+      acc = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(w2t[q], d[q], acc, 0, 0, 0);
+    through_relu(acc, h1, d);
+    wave_lds_fence();
     // gW1[j][k] += sum_s dh1[s][j] x[s][k]
-    g1 = mma32<32>(g1, [&](int j, int s) { return dh1[wave][s * MLP_H + j]; },
-                   [&](int s, int k) { return k < MLP_NI ? T.x[s * MLP_NI + k] : (uint16_t)0; });
-    __builtin_amdgcn_s_waitcnt(0);
-    __builtin_amdgcn_wave_barrier();
+    gb1 += grad_outer(T, T.x, MLP_H, MLP_NI, g1);
+    wave_lds_fence();
   }
-  // per-wave results -> red[wave][...]
-  float* R = red[wave];
+  float* R = reinterpret_cast<float*>(&T);
 #pragma unroll
   for (int r = 0; r < 16; r++) {
     const int i = mrow(l, r), k = mcol(l);
@@ -198,7 +287,7 @@ __global__ __launch_bounds__(64 * MLP_WAVES) void mlp_grad_kernel(
   for (int e = tid; e < MLP_NPARAM + 1; e += blockDim.x) {
     float s = 0.0f;
 #pragma unroll
-    for (int w = 0; w < MLP_WAVES; w++) s += red[w][e];
+    for (int w = 0; w < GRAD_WAVES; w++) s += reinterpret_cast<const float*>(&tiles[w])[e];
     part[(int64_t)blockIdx.x * (MLP_NPARAM + 1) + e] = s;
   }
 }
@@ -206,10 +295,10 @@ __global__ __launch_bounds__(64 * MLP_WAVES) void mlp_grad_kernel(
 // Fixed-order sum of the workgroup partials (nblk rows of MLP_NPARAM + 1).
 // A workgroup sums kRedCols columns: kRedRows row classes (rows r, r +
 // kRedRows, ...) side by side, then the classes in order.  The reads are the
-// whole cost (3.3 MB at 512 rows, 65 536 samples); one lane per column, each
-// walking all rows, left 7 workgroups with one load in flight per lane and
-// took 119 us; this split has 52 workgroups of 16 waves, each lane with four
-// loads in flight: 7.1 us.
+// whole cost (1.7 MB: 256 rows at 65 536 samples); one lane per column, each
+// walking all rows, left 7 workgroups with one load in flight per lane: 119
+// us at 512 rows.  This split has 52 workgroups of 16 waves, each lane with
+// four loads in flight: 7.2 us at 512 rows, 4.7 us at 256.
 constexpr int kRedCols = 32, kRedRows = 32;
 __global__ __launch_bounds__(kRedCols * kRedRows) void mlp_reduce_kernel(const float* part,
                                                                          int nblk, float* grad,
@@ -391,8 +480,8 @@ __global__ void mlp_samples_kernel(const double* U, int64_t n0, int64_t n1, int6
 }  // namespace isw
 
 namespace {
-int grad_blocks(int64_t n) {
-  int64_t b = (n + 32 * isw::MLP_WAVES - 1) / (32 * isw::MLP_WAVES);
+int mlp_blocks(int64_t n, int waves) {
+  int64_t b = (n + 32 * waves - 1) / (32 * waves);
   if (b > 1024) b = 1024;
   if (b < 1) b = 1;
   return (int)b;
@@ -456,8 +545,8 @@ int isweno_mlp_forward(isweno_ctx* ctx, const float* P, const float* X, int64_t 
   if (hipSetDevice(ctx->device) != hipSuccess) return ISWENO_ERR_DEVICE;
   if (n == 0) return ISWENO_OK;
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-  hipLaunchKernelGGL(isw::mlp_forward_kernel, dim3(grad_blocks(n)), dim3(64 * isw::MLP_WAVES), 0,
-                     s, P, X, n, out);
+  hipLaunchKernelGGL(isw::mlp_forward_kernel, dim3(mlp_blocks(n, isw::MLP_WAVES)),
+                     dim3(64 * isw::MLP_WAVES), 0, s, P, X, n, out);
   return hipGetLastError() == hipSuccess ? ISWENO_OK : ISWENO_ERR_DEVICE;
 }
 
@@ -466,7 +555,7 @@ int isweno_mlp_loss_grad(isweno_ctx* ctx, const float* P, const float* X, const 
   if (!ctx || !P || !X || !Y || !loss || !grad || n < 1) return ISWENO_ERR_ARG;
   if (hipSetDevice(ctx->device) != hipSuccess) return ISWENO_ERR_DEVICE;
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-  const int nb = grad_blocks(n);
+  const int nb = mlp_blocks(n, isw::GRAD_WAVES);
   // partial gradients in the context's own buffer (grown on demand; calls
   // on one context do not overlap, see isweno.h)
   if (nb > ctx->mlp_part_blocks) {
@@ -481,7 +570,7 @@ int isweno_mlp_loss_grad(isweno_ctx* ctx, const float* P, const float* X, const 
       return ISWENO_ERR_DEVICE;
     ctx->mlp_part_blocks = nb;
   }
-  hipLaunchKernelGGL(isw::mlp_grad_kernel, dim3(nb), dim3(64 * isw::MLP_WAVES), 0, s, P, X, Y, Cc,
+  hipLaunchKernelGGL(isw::mlp_grad_kernel, dim3(nb), dim3(64 * isw::GRAD_WAVES), 0, s, P, X, Y, Cc,
                      n, ctx->mlp_part);
   if (hipGetLastError() != hipSuccess) return ISWENO_ERR_DEVICE;
   hipLaunchKernelGGL(isw::mlp_reduce_kernel,

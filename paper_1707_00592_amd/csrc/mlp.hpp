@@ -70,7 +70,7 @@ struct MlpTile {
   uint16_t x[32 * MLP_NI];
   uint16_t h1[32 * MLP_H];
   uint16_t h2[32 * MLP_H];
-  float z[32 * 16];  // logits (9 used); reused for dz in training
+  float z[32 * 16];  // logits (9 used)
 };
 
 // Forward pass of one tile (all 64 lanes of the wave take part): x (bf16,

@@ -1,6 +1,7 @@
 """The training gradient's sum over workgroup partials, at the row counts
-where the summing kernel's split changes: one row, fewer rows than row
-classes, one more, more than a lane's loads in flight, and the largest."""
+where the summing kernel's split changes (a row is 256 samples): one row,
+fewer rows than row classes, one more, more than a lane's loads in flight,
+and the largest, where waves take more than one tile."""
 import numpy as np
 import pytest
 
@@ -10,7 +11,8 @@ from test_gpu_mlp import BLOCKS, _dev, _params, _rounded_reference_grad
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("n", [1, 31 * 128, 32 * 128 + 1, 128 * 128 + 1, 1024 * 128 + 33])
+@pytest.mark.parametrize("n", [1, 31 * 128, 32 * 128 + 1, 128 * 128 + 1, 1024 * 128 + 33,
+                               31 * 256, 32 * 256 + 1, 128 * 256 + 1, 1024 * 256 + 33])
 def test_gradient_at_partial_counts(lib, n):
     """Each parameter block within 1e-2 of the reference that rounds to bf16
     where the kernels do (the bound of the gradient-block test)."""
