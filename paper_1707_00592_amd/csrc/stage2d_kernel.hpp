@@ -185,24 +185,29 @@ __global__ __launch_bounds__(kThreads, CUT && GATHER ? 2 : 4) void stage2d_kerne
   const int cy = tid >> 4, cx = tid & 15;  // the lane's cell (cx < 15) and x face
   const bool mine = cx < TX && gx0 + cx < nx && gy0 + cy < ny;
   const int64_t mycell = (gy0 + cy) * nx + gx0 + cx;
-  // the output step of the lane's cell, component kc, from its L and the
-  // stage input there (fetched where the caller does not have it)
-  auto put = [&](int kc, double L, auto uin) {
-    const int64_t o = kc * N + mycell;
-    if (MODE == OUT_RHS || MODE == OUT_RK1L) {
-      g.Rout[o] = L;
-    } else {
-      const double h = *g.dt;
-      if (MODE == OUT_RK1) {
-        g.Uout[o] = g.U0[o] + h * L;
-      } else if (MODE == OUT_RK2) {
-        g.Uout[o] = 0.75 * g.U0[o] + 0.25 * (uin(o) + h * L);
-      } else if (MODE == OUT_RK2L) {
-        const double u0 = g.U0[o];
-        g.Uout[o] = 0.75 * u0 + 0.25 * (uin(o) + h * L);
-      } else {
-        g.Uout[o] = (1.0 / 3.0) * g.U0[o] + (2.0 / 3.0) * (uin(o) + h * L);
+  // the output step of the lane's cell from its L; uin(c) is the stage input
+  // there.  Everything is loaded before anything is stored: the compiler may
+  // not move a load over the store before it, which left a chain of round
+  // trips to memory at the end of every tile.
+  auto put = [&](const double* L, auto uin) {
+    constexpr bool STEP = MODE != OUT_RHS && MODE != OUT_RK1L;
+    double u0[NC], ui[NC];
+    if constexpr (STEP) {
+#pragma unroll
+      for (int c = 0; c < NC; c++) {
+        u0[c] = g.U0[c * N + mycell];
+        if (MODE != OUT_RK1) ui[c] = uin(c);
       }
+    }
+    const double h = STEP ? *g.dt : 0.0;
+#pragma unroll
+    for (int c = 0; c < NC; c++) {
+      const int64_t o = c * N + mycell;
+      if (!STEP) g.Rout[o] = L[c];
+      else if (MODE == OUT_RK1) g.Uout[o] = u0[c] + h * L[c];
+      else if (MODE == OUT_RK2 || MODE == OUT_RK2L)
+        g.Uout[o] = 0.75 * u0[c] + 0.25 * (ui[c] + h * L[c]);
+      else g.Uout[o] = (1.0 / 3.0) * u0[c] + (2.0 / 3.0) * (ui[c] + h * L[c]);
     }
   };
   // a uniform tile (steady_state): every face has the same flux
@@ -211,11 +216,13 @@ __global__ __launch_bounds__(kThreads, CUT && GATHER ? 2 : 4) void stage2d_kerne
     cons_prim<NDIM, T>(ref, q);
     if (steady_state<NDIM>(q)) {
       if (mine) {
+        double L[NC];
 #pragma unroll
-        for (int kc = 0; kc < NC; kc++) {
-          const double t = steady_term(kc >= 4, q[kc]);
-          put(kc, t + t, [&](int64_t) { return ref[kc]; });
+        for (int c = 0; c < NC; c++) {
+          const double t = steady_term(c >= 4, q[c]);
+          L[c] = t + t;
         }
+        put(L, [&](int c) { return ref[c]; });
       }
       if (g.shortcut && (sizeof(T) == 4 || g.eps > 0.0)) {
         // measurement only: every field-side of the tile's faces, each face
@@ -411,16 +418,19 @@ __global__ __launch_bounds__(kThreads, CUT && GATHER ? 2 : 4) void stage2d_kerne
     }
     CellSize<T>(g.dx[0]).template quotients<NC + 2>(x);
     CellSize<T>(g.dx[1]).template quotients<NC + 2>(y);
+    double L[NC];
 #pragma unroll
     for (int kk = 0; kk < NC; kk++) {
       const int kc = axis_comp<NDIM, 1>(kk);
       const double rx = kc >= 4 ? x[kc] + x[kc + 2] : x[kc];
       const double ry = kk >= 4 ? y[kk] + y[kk + 2] : y[kk];
-      put(kc, rx + ry, [&](int64_t o) {
-        if constexpr (FROM_L) return g.U0[o] + h1 * g.R[o];  // as stage 1 would have written it
-        else return g.Uin[o];
-      });
+      L[kc] = rx + ry;
     }
+    put(L, [&](int c) {
+      const int64_t o = c * N + mycell;
+      if constexpr (FROM_L) return g.U0[o] + h1 * g.R[o];  // as stage 1 would have written it
+      else return g.Uin[o];
+    });
   }
 }
 

@@ -255,16 +255,8 @@ __device__ __forceinline__ void wave_max_bits(double m, unsigned long long* red)
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = b;
 }
 
-template <int NDIM>
-__device__ __forceinline__ bool cell_ok(const double* U, int64_t N,
-                                        int64_t cell, const double* q) {
-  bool fin = true;
-#pragma unroll
-  for (int k = 0; k < 4 + NDIM; k++) fin = fin && isfinite(U[k * N + cell]);
-  return fin && admissible(q[0], q[1 + NDIM], q[2 + NDIM], q[3 + NDIM]);
-}
-
-// The same check on a cell's conservative values u (already loaded).
+// Whether a cell (conservative values u, primitives q) is finite and
+// admissible.
 template <int NDIM>
 __device__ __forceinline__ bool cell_ok_u(const double* u, const double* q) {
   bool fin = true;
@@ -286,7 +278,7 @@ __device__ __forceinline__ bool in_range(const double* q) {
   return ok;
 }
 
-// The remaining condition of cell_ok for a cell in_range.
+// The remaining condition of cell_ok_u for a cell in_range.
 template <int NDIM>
 __device__ __forceinline__ bool c2_positive(const double* q) {
   return (q[2 + NDIM] + 1.0) * q[1 + NDIM] + q[3 + NDIM] > 0.0;

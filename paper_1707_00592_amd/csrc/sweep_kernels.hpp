@@ -73,22 +73,33 @@ __device__ __forceinline__ unsigned sweep_tile(unsigned b, unsigned ntiles) {
   return ((k / kSweepRun) * 8 + xcd) * kSweepRun + k % kSweepRun;
 }
 
-// The output step of one cell's component (offset o into the state) from r,
-// this axis' term; uin(o) is the stage input there.
-template <int MODE, bool READ_R, class F>
-__device__ __forceinline__ void sweep_put(const SweepArgs& g, int64_t o, double r, F uin) {
-  const double L = READ_R ? g.R[o] + r : r;
-  if (MODE == OUT_PARTIAL || MODE == OUT_PARTIAL_S || MODE == OUT_RHS) {
-    g.Rout[o] = L;
-  } else {
-    const double h = *g.dt;
-    if (MODE == OUT_RK1) {
-      g.Uout[o] = g.U0[o] + h * L;
-    } else if (MODE == OUT_RK2) {
-      g.Uout[o] = 0.75 * g.U0[o] + 0.25 * (uin(o) + h * L);
-    } else {
-      g.Uout[o] = (1.0 / 3.0) * g.U0[o] + (2.0 / 3.0) * (uin(o) + h * L);
-    }
+// The output step of a cell from this axis' terms r (axis order); uin(c) is
+// the stage input there.  Everything is loaded before anything is stored: the
+// compiler may not move a load over the store before it (the buffers may be
+// one, and are: element by element), which left a chain of NC round trips to
+// memory at the end of every tile.
+template <int MODE, bool READ_R, int NC, class F>
+__device__ __forceinline__ void sweep_put(const SweepArgs& g, int64_t N, int64_t cell,
+                                          const double* r, F uin) {
+  constexpr bool STEP = MODE != OUT_PARTIAL && MODE != OUT_PARTIAL_S && MODE != OUT_RHS;
+  double L[NC], u0[NC], ui[NC];
+#pragma unroll
+  for (int c = 0; c < NC; c++) {
+    const int64_t o = c * N + cell;
+    if (READ_R) L[c] = g.R[o];
+    if (STEP) u0[c] = g.U0[o];
+    if (STEP && MODE != OUT_RK1) ui[c] = uin(c);
+  }
+  const double h = STEP ? *g.dt : 0.0;
+#pragma unroll
+  for (int c = 0; c < NC; c++) L[c] = READ_R ? L[c] + r[c] : r[c];
+#pragma unroll
+  for (int c = 0; c < NC; c++) {
+    const int64_t o = c * N + cell;
+    if (!STEP) g.Rout[o] = L[c];
+    else if (MODE == OUT_RK1) g.Uout[o] = u0[c] + h * L[c];
+    else if (MODE == OUT_RK2) g.Uout[o] = 0.75 * u0[c] + 0.25 * (ui[c] + h * L[c]);
+    else g.Uout[o] = (1.0 / 3.0) * u0[c] + (2.0 / 3.0) * (ui[c] + h * L[c]);
   }
 }
 
@@ -147,10 +158,10 @@ __device__ __forceinline__ bool sweep_steady(const SweepArgs& g,
     const int j = D == 0 ? e % TL : e / TW;
     if (w >= cells.na || j >= cells.nl) continue;
     const int64_t cell = cells.cell(w, j + 3);
+    double r[NC];
 #pragma unroll
-    for (int c = 0; c < NC; c++)
-      sweep_put<MODE, READ_R>(g, c * N + cell, steady_term(c >= NC - 2, q[c]),
-                              [&](int64_t) { return ref[c]; });
+    for (int c = 0; c < NC; c++) r[c] = steady_term(c >= NC - 2, q[c]);
+    sweep_put<MODE, READ_R, NC>(g, N, cell, r, [&](int c) { return ref[c]; });
   }
   if (g.shortcut && threadIdx.x == 0 && (sizeof(T) == 4 || g.eps > 0.0)) {
     // measurement only: every field-side of the tile's faces, each face
@@ -220,6 +231,11 @@ __global__ __launch_bounds__(NTHR, MODE == OUT_PARTIAL_S ? 5 : 1) void sweep_ker
   // 1. stage primitives (FP64) with ghost cells
   int found = tid == 0 && latched(g.stats) ? TILE_SKIP : 0;
   double m = 0.0;  // SPEEDS: the lane's max wave speed
+  // Uniform tiles are not looked for in the float form's 3D sweeps: they run
+  // close to the memory's rate, flat stencils make their faces cheap already,
+  // and tiles without faces only bunch up the traffic (256^3 droplet, x sweep
+  // 447 us without, 518 with; y 561 and 600; z 807 and 838).
+  constexpr bool UNIFORM = !(NDIM == 3 && sizeof(T) == 4);
   const double dxs[3] = {g.dx[0], g.dx[1], g.dx[2]};
   double ref[NC];  // the tile's first cell
 #pragma unroll
@@ -234,7 +250,7 @@ __global__ __launch_bounds__(NTHR, MODE == OUT_PARTIAL_S ? 5 : 1) void sweep_ker
     double u[NC], q[NC];
 #pragma unroll
     for (int c = 0; c < NC; c++) u[c] = g.Uin[c * N + cell];
-    found |= differs<NC, sizeof(T) == 8>(u, ref, flip);
+    if constexpr (UNIFORM) found |= differs<NC, sizeof(T) == 8>(u, ref, flip);
     cons_prim<NDIM, T>(u, q);
     const bool inr = sizeof(T) == 8 && in_range<NDIM>(q);
     if constexpr (sizeof(T) == 8) found |= inr ? 0 : TILE_FAR;
@@ -267,7 +283,7 @@ __global__ __launch_bounds__(NTHR, MODE == OUT_PARTIAL_S ? 5 : 1) void sweep_ker
     }
   }
 
-  if (!(notes & TILE_MIXED) &&
+  if (UNIFORM && !(notes & TILE_MIXED) &&
       sweep_steady<T, NDIM, D, TL, TW, NTHR, MODE, READ_R>(g, cells, N, ref))
     return;
 
@@ -351,11 +367,11 @@ __global__ __launch_bounds__(NTHR, MODE == OUT_PARTIAL_S ? 5 : 1) void sweep_ker
       }
     }
     dx.template quotients<NC + 2>(x);
+    double r[NC];
 #pragma unroll
     for (int k = 0; k < NC; k++)
-      sweep_put<MODE, READ_R>(g, axis_comp<NDIM, D>(k) * N + cell,
-                              k >= NC - 2 ? x[k] + x[k + 2] : x[k],
-                              [&](int64_t o) { return g.Uin[o]; });
+      r[axis_comp<NDIM, D>(k)] = k >= NC - 2 ? x[k] + x[k + 2] : x[k];
+    sweep_put<MODE, READ_R, NC>(g, N, cell, r, [&](int c) { return g.Uin[c * N + cell]; });
   }
 }
 
@@ -496,11 +512,11 @@ __global__ __launch_bounds__(NTHR) void sweep_mlp_kernel(SweepArgs g) {
       }
     }
     dx.template quotients<NC + 2>(x);
+    double r[NC];
 #pragma unroll
     for (int k = 0; k < NC; k++)
-      sweep_put<MODE, READ_R>(g, axis_comp<NDIM, D>(k) * N + cell,
-                              k >= NC - 2 ? x[k] + x[k + 2] : x[k],
-                              [&](int64_t o) { return g.Uin[o]; });
+      r[axis_comp<NDIM, D>(k)] = k >= NC - 2 ? x[k] + x[k + 2] : x[k];
+    sweep_put<MODE, READ_R, NC>(g, N, cell, r, [&](int c) { return g.Uin[c * N + cell]; });
   }
 }
 
