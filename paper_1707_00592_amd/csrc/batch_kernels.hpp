@@ -120,7 +120,7 @@ __global__ __launch_bounds__(TL + 1, sizeof(T) == 4 ? 6 : 1) void batch_stage_ke
     if (!(notes & TILE_MIXED)) {
       double q[NC];
       cons_prim<1, T>(ref, q);
-      if (steady_state<1>(q)) {
+      if (steady_state<T, 1>(q, g.eps)) {
         for (int j = tid; j < len; j += NTHR)
 #pragma unroll
           for (int c = 0; c < NC; c++)
@@ -286,7 +286,7 @@ __global__ __launch_bounds__(NTHR, 4) void batch_step_kernel(BatchArgs g) {
       // stage, and the stages' states stay uniform
       double qr[NC];
       cons_prim<1, T>(ref, qr);
-      if (steady_state<1>(qr)) {
+      if (steady_state<T, 1>(qr, g.eps)) {
         if (mine >= 0 && mine < len) {
 #pragma unroll
           for (int c = 0; c < NC; c++) {

@@ -214,7 +214,7 @@ __global__ __launch_bounds__(kThreads, CUT && GATHER ? 2 : 4) void stage2d_kerne
   if (!(notes & TILE_MIXED)) {
     double q[NC];
     cons_prim<NDIM, T>(ref, q);
-    if (steady_state<NDIM>(q)) {
+    if (steady_state<T, NDIM>(q, g.eps)) {
       if (mine) {
         double L[NC];
 #pragma unroll
@@ -224,7 +224,7 @@ __global__ __launch_bounds__(kThreads, CUT && GATHER ? 2 : 4) void stage2d_kerne
         }
         put(L, [&](int c) { return ref[c]; });
       }
-      if (g.shortcut && (sizeof(T) == 4 || g.eps > 0.0)) {
+      if (g.shortcut) {
         // measurement only: every field-side of the tile's faces, each face
         // counted once (in the tile after it)
         const int64_t w = nx - gx0 < TX ? nx - gx0 : TX, h = ny - gy0 < TY ? ny - gy0 : TY;

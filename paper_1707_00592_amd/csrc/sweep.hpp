@@ -298,8 +298,12 @@ __device__ __forceinline__ bool c2_positive(const double* q) {
 // Such a tile costs its loads and stores (1024x512 at the start of a run, nine
 // tenths of it uniform: 45 us a stage against 69; fully mixed states pay one
 // comparison per staged cell, below what two runs differ by).
-template <int NDIM>
-__device__ __forceinline__ bool steady_state(const double* q) {
+// FP64 with epsilon = 0 is left to the faces: a constant stencil's weights
+// are 0/0 there, and its tile's NaNs and fallbacks are the method's (the float
+// form's flat stencils return their centre value whatever epsilon is).
+template <typename T, int NDIM>
+__device__ __forceinline__ bool steady_state(const double* q, double eps) {
+  if (sizeof(T) == 8 && !(eps > 0.0)) return false;
   const double rho = q[0], p = q[1 + NDIM], G = q[2 + NDIM], P = q[3 + NDIM];
   const double stiff = (G + 1.0) * p + P, gr = G * rho;
   bool ok = rho >= 0x1p-12 && rho <= 0x1p12 && G >= 0x1p-6 && G <= 0x1p6 &&

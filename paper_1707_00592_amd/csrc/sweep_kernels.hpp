@@ -152,7 +152,7 @@ __device__ __forceinline__ bool sweep_steady(const SweepArgs& g,
   constexpr int NC = 4 + NDIM;
   double q[NC];
   cons_prim<NDIM, T>(ref, q);
-  if (!steady_state<NDIM>(q)) return false;
+  if (!steady_state<T, NDIM>(q, g.eps)) return false;
   for (int e = threadIdx.x; e < TW * TL; e += NTHR) {
     const int w = D == 0 ? e / TL : e % TW;
     const int j = D == 0 ? e % TL : e / TW;
@@ -163,7 +163,7 @@ __device__ __forceinline__ bool sweep_steady(const SweepArgs& g,
     for (int c = 0; c < NC; c++) r[c] = steady_term(c >= NC - 2, q[c]);
     sweep_put<MODE, READ_R, NC>(g, N, cell, r, [&](int c) { return ref[c]; });
   }
-  if (g.shortcut && threadIdx.x == 0 && (sizeof(T) == 4 || g.eps > 0.0)) {
+  if (g.shortcut && threadIdx.x == 0) {
     // measurement only: every field-side of the tile's faces, each face
     // counted once (in the tile after it)
     atomicAdd(&g.shortcut[(blockIdx.x & 255) * 3 + D],

@@ -111,3 +111,52 @@ def test_batch_of_uniform_and_mixed_tubes(lib, ctx):
             h = oracle.cfl_dt(W, og, oracle.make_opts())
             W, _ = oracle.rk3_step(W, og, h, oracle.make_opts())
         assert _same_bits(got[:, off[k]:off[k + 1]], W), n
+
+
+def _same_or_nan(a, b):
+    """Equal bits, NaN where the other is NaN."""
+    return np.array_equal(np.isnan(a), np.isnan(b)) and _same_bits(np.where(np.isnan(a), 0.0, a),
+                                                                   np.where(np.isnan(b), 0.0, b))
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+@pytest.mark.parametrize("mood", [False, True])
+@pytest.mark.parametrize("weights", [oracle.W_MODIFIED, oracle.W_BASIC])
+def test_epsilon_zero_is_not_skipped(lib, ctx, shape, mood, weights):
+    """epsilon = 0: a constant stencil's weights are 0/0, so a uniform tile's
+    derivative is NaN without the cascade and each of its face sides falls
+    back with it, as everywhere else."""
+    d = len(shape)
+    dx = tuple(1.0 / m for m in shape)
+    ig, og = lib.make_grid(shape, dx, 0, 0), oracle.make_grid(shape, dx, (0,) * d, (0,) * d)
+    o = lib.make_opts(weights=weights, mood=mood, eps=0.0)
+    oo = oracle.make_opts(weights=weights, mood=mood, eps=0.0)
+    for k in range(2):
+        U = _uniform(shape, STATES[k], k)
+        if k:  # mixed and uniform tiles side by side
+            U[:, U.shape[1] // 2] *= 1.001
+        st = lib.new_stats()
+        got = ctx.rhs(_dev(U), ig, o, stats=st).cpu().numpy()
+        ref, so = oracle.rhs(U, og, oo)
+        assert np.isnan(ref).any() != mood and _same_or_nan(got, ref), k
+        s = lib.read_stats(st)
+        assert (list(s.o3), list(s.o1)) == (list(so.o3), list(so.o1)) and any(so.o1) == mood
+
+
+@pytest.mark.parametrize("bc", [0, 1])
+def test_epsilon_zero_batch(lib, ctx, bc):
+    """The same in a batch, whole steps and stage launches."""
+    import torch
+    sizes = [40, 700, 255]
+    off = np.concatenate([[0], np.cumsum(sizes)])
+    U = _uniform((int(off[-1]),), STATES[0], 0)
+    dxs = np.array([1.0 / n for n in sizes])
+    ref, dtr, so, s, ps = oracle.batch_step(U, off, dxs, oracle.make_opts(eps=0.0), bc_lo=bc,
+                                            bc_hi=bc, pstatus=np.zeros(3, np.intc))
+    plan, V, st = ctx.batch_plan(off, dxs, bc, bc), _dev(U), lib.new_stats()
+    dt = torch.zeros(3, dtype=torch.float64, device="cuda")
+    plan.step(V, lib.make_opts(eps=0.0), dt, 1, st)
+    assert list(plan.status.cpu().numpy()) == list(ps) == [0, 0, 0]
+    assert _same_bits(V.cpu().numpy(), ref)
+    got = lib.read_stats(st)
+    assert (got.o3[0], got.o1[0]) == (so.o3[0], so.o1[0]) and so.o1[0] > 0
