@@ -26,6 +26,20 @@ struct Step1dArgs {
   unsigned long long* shortcut;  // 256 x 3 counters of shortcut field-sides, or null
 };
 
+// A cell's (|u| + c) / dx of eq. (2)'s primitives, as cfl_kernel forms it.
+// The step's dt is isweno_cfl_dt's value in both forms, so the two products
+// an add follows are rounded (opaque) also where the float form's kernels are
+// compiled with contraction.
+__device__ __forceinline__ double line_speed(const double* u, double dx) {
+  const double rho = u[0], G = u[3], P = u[4], vel = u[1] / rho;
+  double ke = 0.5 * rho * (vel * vel);
+  opaque(ke);
+  const double p = (u[2] - ke - P) / G;
+  double gp = (G + 1.0) * p;
+  opaque(gp);
+  return (fabs(vel) + sqrt((gp + P) / (G * rho))) / dx;
+}
+
 template <typename T, int NTHR, bool CUT>
 __global__ __launch_bounds__(NTHR) void step1d_kernel(Step1dArgs g) {
   constexpr int NC = 5, NP = NTHR + 6, NW = NTHR / 64;
@@ -48,11 +62,9 @@ __global__ __launch_bounds__(NTHR) void step1d_kernel(Step1dArgs g) {
   for (int c = 0; c < NC; c++) u[c] = u0[c] = cell ? g.U[(int64_t)c * n + tid] : 1.0;
   double h;
   if (g.cfl > 0.0) {
-    // the time step as cfl_kernel forms it
-    double q[NC], m = 0.0;
-    cons_prim<1>(u0, q);
+    double m = 0.0;
     if (cell) {
-      const double sp = cell_speed<1>(q, &g.dx);
+      const double sp = line_speed(u0, g.dx);
       m = (sp > m || sp != sp) ? sp : m;
     }
     wave_max_bits(m, s_red);

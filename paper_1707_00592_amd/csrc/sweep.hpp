@@ -74,7 +74,10 @@ __device__ __forceinline__ int wave_sum(int v) {
 }
 
 // A value the compiler may not reason about (no instruction).
-__device__ __forceinline__ void opaque(int64_t& v) { asm("" : "+v"(v)); }
+template <typename V>
+__device__ __forceinline__ void opaque(V& v) {
+  asm("" : "+v"(v));
+}
 
 // Boundary map of a ghost/interior position l, a few cells at most outside
 // the line of n cells (-3..n+2): interior index and whether the normal
