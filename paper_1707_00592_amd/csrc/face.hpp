@@ -549,6 +549,33 @@ __device__ __forceinline__ double weno_f64_cutoff(double a, double b, double c, 
   return q;
 }
 
+// The 3rd-order reconstruction of a side that failed, in the range of
+// weno_f64_unit (the same face), whose reasons for the linear form hold.
+template <bool CUT>
+__device__ __forceinline__ double weno_f64_unit3(double a, double b, double c, double d, double e,
+                                                 int weights, double eps) {
+  const TauUnit t = tau_unit(a, b, c, d, e);
+  const double c1 = (1.0 / 2.0) * c + (1.0 / 2.0) * d;
+  const double c2 = -(1.0 / 2.0) * b + (3.0 / 2.0) * c;
+  if constexpr (CUT) {
+    const int mask = t.tau < 0x1p-60 * eps
+                         ? 3
+                         : cut_mask_f64<true>(indicators_unit(t, a, b, c, d, e), eps, true);
+    return kCutWeights.w[mask][0] * c1 + kCutWeights.w[mask][1] * c2;
+  } else {
+    if (t.tau < 0x1p-60 * eps) {
+      constexpr double s3 = ISW_D1 + ISW_D2;
+      return (ISW_D1 / s3) * c1 + (ISW_D2 / s3) * c2;
+    }
+    const Ind<double> s = indicators_unit(t, a, b, c, d, e);
+    const double r12 = weights == W_BASIC ? 1.0 : divide(s.tau, recip(s.b12 + eps));
+    const double a1 = ISW_D1 * (1.0 + divide(s.tau, recip(s.b1 + eps)) * r12);
+    const double a2 = ISW_D2 * (1.0 + divide(s.tau, recip(s.b2 + eps)) * r12);
+    const Recip rs = recip(a1 + a2);
+    return divide(a1, rs) * c1 + divide(a2, rs) * c2;
+  }
+}
+
 // weno_f64_unit's counterpart for the cut-off weights.
 __device__ __forceinline__ double weno_f64_cutoff_unit(double a, double b, double c, double d,
                                                        double e, double eps, int& nlin) {

@@ -698,29 +698,80 @@ __device__ __forceinline__ void states_flux(const double* ql, const double* qr, 
   us = double(tus);
 }
 
-// An FP64 face of a tile in range, 5th order and no cascade.  Returns true
-// when that is not the face's flux: a sound speed outside the range of the
-// unscaled divisions or (mood) a state that fails the positivity check; it
-// is then evaluated by face_general.  The two share no value: with the
-// general reconstruction and the cascade behind a branch inside this path the
-// 2D stage took 5-8% longer on states that never reach them.
+// The cascade of an FP64 face in range: the sides that failed (bit 0 left, bit
+// 1 right) in 3rd order.  Rolled over fields and sides, which keeps the states
+// and the loop in the registers of the 5th-order path: unrolled behind a branch
+// there it cost states that never reach it 5-8%, and with the whole face
+// evaluated again apart from it (in 5th order as well) the slowest wave of a
+// small batch took three face evaluations a stage: 60 tubes of 100 to 600
+// cells 61 us a step, 51 so; 1024x512, a tenth of the cells random, 204 us a
+// stage, 166 so.
 template <int NDIM, int D, bool CUT, class S>
-__device__ __forceinline__ bool face_common(const S& st, const TileState& tile, int weights,
-                                            int mood, double eps, double* F, double& us,
-                                            int& nshort) {
+__device__ __forceinline__ void recon_cascade(const S& st, int sides, int weights, double eps,
+                                              double a, double b, double bd, double gd,
+                                              double* ql, double* qr) {
   constexpr int NT = NDIM - 1, NC = 5 + NT;
-  double a, b, bd, gd, ql[NC], qr[NC];
+  constexpr int CR = 0, CU = 1 + D, CP = 1 + NDIM;
+#pragma unroll 1
+  for (int m = 0; m < NC; m++) {
+    // the field's row of L: x times component c plus y times p, or a copy of c
+    const bool copy = m >= 2 && m < NC - 1;
+    const int c = m == 1 ? CR : !copy ? CU : m < 2 + NT ? 1 + ((m - 2) < D ? m - 2 : m - 1) : m + 1;
+    const double x = m == 0 ? -a : m == 1 ? 1.0 : a, y = m == 1 ? -b : 0.5;
+#pragma unroll 1
+    for (int side = 0; side < 2; side++) {
+      if (!(sides & (1 << side))) continue;
+      double w[5];
+      // (opaque: or all six pressures are loaded before the loops and kept)
+      int cc = c, cp = CP;
+      asm("" : "+s"(cc), "+s"(cp));
+#pragma unroll
+      for (int j = 0; j < 5; j++) {
+        const int at = side ? 5 - j : j;
+        w[j] = st(cc, at);
+        if (!copy) w[j] = x * w[j] + y * st(cp, at);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      const double r = weno_f64_unit3<CUT>(w[0], w[1], w[2], w[3], w[4], weights, eps);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int k = 0; k < NC; k++)
+        if (k == m) {
+          if (side) back_project<NT>(k, r, bd, gd, qr);
+          else back_project<NT>(k, r, bd, gd, ql);
+        }
+    }
+  }
+}
+
+// The states of an FP64 face of a tile in range, with the cascade (mood).
+// Returns true when the sound speed lies outside the range of the unscaled
+// divisions; the face is then evaluated by face_general, which shares no value
+// with this path.
+template <int NDIM, int D, bool CUT, class S>
+__device__ __forceinline__ bool common_states(const S& st, const TileState& tile, int weights,
+                                              int mood, double eps, double* ql, double* qr,
+                                              int& n3, int& n1, int& nshort) {
+  constexpr int NT = NDIM - 1;
+  double a, b, bd, gd;
   face_params<double, NDIM>(st, a, b, bd, gd);
   nshort = 0;
   // b = 1/c^2 of the mean state: c^2 >= kFaceC2Min
-  bool bad = !(b > 0.0 && b <= 1.0 / kFaceC2Min);
+  const bool far = !(b > 0.0 && b <= 1.0 / kFaceC2Min);
   if (!CUT && weights == W_BASIC)
     recon_fast<NDIM, D, CUT, true>(st, tile.one_fluid, eps, a, b, bd, gd, ql, qr, nshort);
   else
     recon_fast<NDIM, D, CUT, false>(st, tile.one_fluid, eps, a, b, bd, gd, ql, qr, nshort);
-  bad = bad || (mood && mood_fail<NT>(ql, qr));
-  states_flux<double, NT>(ql, qr, F, us);
-  return bad;
+  n3 = 0;
+  n1 = 0;
+  if (mood) {
+    const int fail = far ? 0 : mood_fail<NT>(ql, qr);
+    if (__builtin_expect(__any(fail), 0)) {
+      recon_cascade<NDIM, D, CUT>(st, fail, weights, eps, a, b, bd, gd, ql, qr);
+      first_order<NDIM, D>(st, fail, ql, qr, n3, n1);
+    }
+  }
+  return far;
 }
 
 // An FP64 face in general: any range, with the cascade.
@@ -749,8 +800,8 @@ __device__ __forceinline__ void face_general(const S& st, int weights, int mood,
 // Full face: average state, eigen-parameters, both reconstructions, MOOD
 // cascade, HLLC.  F (face order) and us are written; n3/n1 report the
 // orders used (per side), nshort the field-sides of the first pass whose
-// reconstruction took its shortcut.  FP64: a wave with a face that is not
-// face_common's evaluates all its faces by face_general (the same bits).
+// reconstruction took its shortcut.  FP64: a wave with a face out of range
+// evaluates all its faces by face_general (the same bits).
 template <typename T, int NDIM, int D, bool CUT = false, class S>
 __device__ __forceinline__ void face_flux(const S& st, const TileState& tile, int weights,
                                           int mood, double eps, double* F, double& us,
@@ -759,11 +810,13 @@ __device__ __forceinline__ void face_flux(const S& st, const TileState& tile, in
   constexpr int NT = NDIM - 1, NC = 5 + NT;
   if constexpr (sizeof(T) == 8) {
     bool other = true;
-    n3 = 0;
-    n1 = 0;
-    if (tile.fast) other = face_common<NDIM, D, CUT>(st, tile, weights, mood, eps, F, us, nshort);
-    if (__any(other)) face_general<NDIM, D, CUT>(st, weights, mood, eps, F, us, n3, n1, nshort);
-    return;
+    if (tile.fast) {
+      double ql[5 + NT], qr[5 + NT];
+      other = common_states<NDIM, D, CUT>(st, tile, weights, mood, eps, ql, qr, n3, n1, nshort);
+      states_flux<double, NT>(ql, qr, F, us);
+    }
+    if (__builtin_expect(__any(other), 0))
+      face_general<NDIM, D, CUT>(st, weights, mood, eps, F, us, n3, n1, nshort);
   } else {
   T a, b;
   double bd, gd, ql[NC], qr[NC];
@@ -807,8 +860,8 @@ __device__ __forceinline__ void face_flux(const S& st, const TileState& tile, in
 // 5th-order states and their check; a face with a failing side returns its
 // fail bits (non-zero) and no flux.  Second pass (face_flux_redo, on the
 // gathered faces): the whole face again with the cascade -- the flux that
-// face_flux gives, bit for bit.  FP64: a face face_common does not evaluate
-// is gathered as well, and the second pass is face_general.
+// face_flux gives, bit for bit.  FP64: a face out of range is gathered as
+// well, and the second pass is face_general.
 template <typename T, int NDIM, int D, bool CUT = false, class S>
 __device__ __forceinline__ int face_flux_first(const S& st, const TileState& tile, int weights,
                                                double eps, double* F, double& us, int& nshort) {
@@ -816,7 +869,12 @@ __device__ __forceinline__ int face_flux_first(const S& st, const TileState& til
   nshort = 0;
   if constexpr (sizeof(T) == 8) {
     if (!tile.fast) return 1;
-    return face_common<NDIM, D, CUT>(st, tile, weights, 1, eps, F, us, nshort) ? 1 : 0;
+    double ql[5 + NT], qr[5 + NT];
+    int n3, n1;
+    if (common_states<NDIM, D, CUT>(st, tile, weights, 0, eps, ql, qr, n3, n1, nshort)) return 1;
+    if (const int fail = mood_fail<NT>(ql, qr)) return fail;
+    states_flux<double, NT>(ql, qr, F, us);
+    return 0;
   } else {
     T a, b;
     double bd, gd, ql[NC], qr[NC];
