@@ -200,6 +200,7 @@ __global__ __launch_bounds__(NTHR, MODE == OUT_PARTIAL_S ? 5 : 1) void sweep_ker
   T* const sq = reinterpret_cast<T*>(lds);
   T* const sf = reinterpret_cast<T*>(lds + SF_OFF);
   __shared__ TileNotes<NTHR / 64> s_notes;
+  __shared__ unsigned s_mood;  // the tile's fallbacks
   // OUT_PARTIAL_S: this x sweep also finds its tile's max wave speed (the
   // step's time step; the tiles of an x sweep hold every cell once)
   constexpr bool SPEEDS = MODE == OUT_PARTIAL_S;
@@ -228,6 +229,7 @@ __global__ __launch_bounds__(NTHR, MODE == OUT_PARTIAL_S ? 5 : 1) void sweep_ker
   // go out ahead of the resident workgroups' arithmetic), normal afterwards
   // (the float sweeps ran slower with it)
   if constexpr (sizeof(T) == 8) __builtin_amdgcn_s_setprio(1);
+  if (tid == 0) s_mood = 0u;
   // 1. stage primitives (FP64) with ghost cells
   int found = tid == 0 && latched(g.stats) ? TILE_SKIP : 0;
   double m = 0.0;  // SPEEDS: the lane's max wave speed
@@ -331,14 +333,9 @@ __global__ __launch_bounds__(NTHR, MODE == OUT_PARTIAL_S ? 5 : 1) void sweep_ker
       sf[fidx(NC, fw, fj)] = T(us);
     }
   }
-  if (g.stats && g.mood) {
-    const unsigned long long b3 = __ballot(my3 != 0);
-    const unsigned long long b1 = __ballot(my1 != 0);
-    if (b3 | b1) {
-      if (my3) atomicAdd(&g.stats->o3[D], (unsigned long long)my3);
-      if (my1) atomicAdd(&g.stats->o1[D], (unsigned long long)my1);
-    }
-  }
+  // (fallbacks: one atomic per workgroup and counter, as in the 2D stage)
+  const bool count = g.stats && g.mood;
+  if (count && __any((my3 | my1) != 0)) atomicAdd(&s_mood, (unsigned)(my3 | my1 << 16));
   if (g.shortcut) {
     // measurement only: one atomic per wave, spread over 256 slots
     const int ws = wave_sum(mys);
@@ -347,6 +344,11 @@ __global__ __launch_bounds__(NTHR, MODE == OUT_PARTIAL_S ? 5 : 1) void sweep_ker
       atomicAdd(&g.shortcut[(blk & 255) * 3 + D], (unsigned long long)ws);
   }
   __syncthreads();
+  if (count && tid == 0 && s_mood) {
+    const unsigned n3 = s_mood & 0xffff, n1 = s_mood >> 16;
+    if (n3) atomicAdd(&g.stats->o3[D], (unsigned long long)n3);
+    if (n1) atomicAdd(&g.stats->o1[D], (unsigned long long)n1);
+  }
 
   // 3. cells
   const CellSize<T> dx(g.dx[D]);
