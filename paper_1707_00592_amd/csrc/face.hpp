@@ -230,12 +230,17 @@ __device__ __forceinline__ double weno_f64_shared_recip(const Ind<double>& s, do
          divide(al.a4, rs) * c4;
 }
 
-// Eq. (19) when the global indicator tau5 of eq. (25) is exactly zero
-// (epsilon > 0): every ratio tau5/(beta + epsilon) of eqs. (21) and (28) is
-// then exactly zero, every weight exactly d_k, and the normalisation
-// divides by the same sum on every such stencil -- the linear scheme, which
-// the indicators select on data with vanishing third and fourth
-// differences -- every stencil of equal values, among others.
+// Whether the global indicator tau5 of eq. (25) leaves the linear scheme:
+// zero, or below 2^-60 epsilon (epsilon > 0).  Every ratio tau5/(beta +
+// epsilon) of eqs. (21) and (28) is then below 2^-59, 1 + ratio rounds to 1,
+// every weight is exactly d_k and the normalisation divides by the same sum on
+// every such stencil.  One rule for every path that counts or takes it.
+__device__ __forceinline__ bool linear_f64(double tau, double eps) {
+  return eps > 0.0 && (tau == 0.0 || tau < 0x1p-60 * eps);
+}
+
+// Eq. (19) on such a stencil: data with vanishing third and fourth
+// differences, every stencil of equal values among others.
 // The candidates of eq. (20) are formed as in the general path and
 // combined in its order with d_k / sum_j d_j (divided at compile time,
 // correctly rounded as the general path divides): the same bits without
@@ -253,15 +258,15 @@ __device__ __forceinline__ double weno_f64_linear(double a, double b, double c, 
          (ISW_D4 / s5) * c4;
 }
 
-// FP64 reconstruction as used by the stage kernels: stencils with tau5 = 0
-// take the linear form (no other indicator is needed); the others the
+// FP64 reconstruction of a face in general: stencils of the linear scheme
+// (linear_f64) take its form (no other indicator is needed); the others the
 // shared-reciprocal form, recomputed with the plain divisions (weno_f64) on
 // the lanes outside its range.  The branches diverge per lane; a wave skips
 // a branch no lane needs.  nlin counts the stencils of the linear form.
 __device__ __forceinline__ double weno_f64_fast(double a, double b, double c, double d,
                                                 double e, int weights, double eps,
                                                 bool order3, int& nlin) {
-  if (eps > 0.0 && tau5<double>(a, b, c, d, e) == 0.0) {
+  if (linear_f64(tau5<double>(a, b, c, d, e), eps)) {
     nlin++;
     return weno_f64_linear(a, b, c, d, e, order3);
   }
@@ -523,8 +528,8 @@ __device__ __forceinline__ int cut_mask_f64(const Ind<double>& s, double eps, bo
   return (p1 >= th ? 1 : 0) | (p2 >= th ? 2 : 0) | (p3 >= th ? 4 : 0) | (p4 >= th ? 8 : 0);
 }
 
-// FP64 cut-off reconstruction as used by the kernels.  Stencils with
-// tau5 = 0 keep every stencil (every ratio is zero) and take the weights of
+// The same for the cut-off weights.  Stencils of the linear scheme
+// keep every candidate (every ratio is next to zero) and take the weights of
 // the full set as compile-time constants.  The others take the FAST mask;
 // lanes outside its range redo the whole reconstruction with the plain
 // divisions (a separate path, as in weno_f64_fast, keeps the common path's
@@ -532,7 +537,7 @@ __device__ __forceinline__ int cut_mask_f64(const Ind<double>& s, double eps, bo
 __device__ __forceinline__ double weno_f64_cutoff(double a, double b, double c, double d,
                                                   double e, double eps, bool order3,
                                                   int& nlin) {
-  if (eps > 0.0 && tau5<double>(a, b, c, d, e) == 0.0) {
+  if (linear_f64(tau5<double>(a, b, c, d, e), eps)) {
     nlin++;
     constexpr CutWeights W = make_cut_weights();
     const double c1 = (1.0 / 2.0) * c + (1.0 / 2.0) * d;

@@ -289,7 +289,7 @@ __global__ __launch_bounds__(kThreads, CUT && GATHER ? 2 : 4) void stage2d_kerne
         double G[NC], vs;
         int nsc;
         fail = face_flux_first<T, NDIM, 1, CUT>(ystencil(tid), tile, wts, g.eps, G, vs, nsc);
-        if (ycounted(tid)) mys[1] += nsc;
+        if (!fail && ycounted(tid)) mys[1] += nsc;
         if (!fail) storey(tid, G, vs);
       }
       enqueue(1, tid, fail);
@@ -299,11 +299,12 @@ __global__ __launch_bounds__(kThreads, CUT && GATHER ? 2 : 4) void stage2d_kerne
       if (tid < nq) {
         const int f = s_queue[tid] & 0xffff, fl = s_queue[tid] >> 16;
         double G[NC], vs;
-        int n3, n1;
-        face_flux_redo<T, NDIM, 1, CUT>(ystencil(f), fl, wts, g.eps, G, vs, n3, n1);
+        int n3, n1, nsc;
+        face_flux_redo<T, NDIM, 1, CUT>(ystencil(f), fl, wts, g.eps, G, vs, n3, n1, nsc);
         if (ycounted(f)) {
           my3[1] += n3;
           my1[1] += n1;
+          mys[1] += nsc;
         }
         storey(f, G, vs);
       }
@@ -335,7 +336,7 @@ __global__ __launch_bounds__(kThreads, CUT && GATHER ? 2 : 4) void stage2d_kerne
     if (xvalid) {
       int nsc;
       fail = face_flux_first<T, NDIM, 0, CUT>(xstencil(tid), tile, wts, g.eps, F, us, nsc);
-      if (xcounted(tid)) mys[0] += nsc;
+      if (!fail && xcounted(tid)) mys[0] += nsc;
     }
     enqueue(0, tid, fail);
     __syncthreads();
@@ -344,11 +345,12 @@ __global__ __launch_bounds__(kThreads, CUT && GATHER ? 2 : 4) void stage2d_kerne
       if (tid < nq) {
         const int f = s_queue[tid] & 0xffff, fl = s_queue[tid] >> 16;
         double Fq[NC], uq;
-        int n3, n1;
-        face_flux_redo<T, NDIM, 0, CUT>(xstencil(f), fl, wts, g.eps, Fq, uq, n3, n1);
+        int n3, n1, nsc;
+        face_flux_redo<T, NDIM, 0, CUT>(xstencil(f), fl, wts, g.eps, Fq, uq, n3, n1, nsc);
         if (xcounted(f)) {
           my3[0] += n3;
           my1[0] += n1;
+          mys[0] += nsc;
         }
 #pragma unroll
         for (int kk = 0; kk < NC; kk++) sfx[kk * NFX + f] = T(Fq[kk]);

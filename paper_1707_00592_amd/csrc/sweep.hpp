@@ -887,21 +887,22 @@ __device__ __forceinline__ int face_flux_first(const S& st, const TileState& til
   }
 }
 
-// fail: face_flux_first's; nshort the first pass's count, replaced where
-// this pass forms the first one's states anew.
+// fail: face_flux_first's; nshort counts the 5th-order states formed again
+// (the first pass's count goes for the faces it settled).
 template <typename T, int NDIM, int D, bool CUT = false, class S>
 __device__ __forceinline__ void face_flux_redo(const S& st, int fail, int weights, double eps,
-                                               double* F, double& us, int& n3, int& n1) {
+                                               double* F, double& us, int& n3, int& n1,
+                                               int& nshort) {
   constexpr int NT = NDIM - 1, NC = 5 + NT;
   if constexpr (sizeof(T) == 8) {
-    int nsc;
-    face_general<NDIM, D, CUT>(st, weights, 1, eps, F, us, n3, n1, nsc);
+    face_general<NDIM, D, CUT>(st, weights, 1, eps, F, us, n3, n1, nshort);
   } else {
     T a, b;
     double bd, gd, ql[NC], qr[NC];
     face_params<T, NDIM>(st, a, b, bd, gd);
-    int nsc = 0, nf3 = 0;
-    recon<T, NDIM, D, CUT>(st, 3, false, weights, T(eps), a, b, bd, gd, ql, qr, nsc);
+    int nf3 = 0;
+    nshort = 0;
+    recon<T, NDIM, D, CUT>(st, 3, false, weights, T(eps), a, b, bd, gd, ql, qr, nshort);
     recon<T, NDIM, D, CUT>(st, fail, true, weights, T(eps), a, b, bd, gd, ql, qr, nf3);
     n3 = 0;
     n1 = 0;
