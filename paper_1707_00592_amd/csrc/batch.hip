@@ -23,6 +23,11 @@
 
 namespace isw {
 
+// Start of a step, one workgroup per problem: a problem is advanced in this
+// step when its status is still OK (active[p]); then, when cfl > 0,
+// dt[p] = cfl / max_cells (|u| + c)/dx_p (clipped to dt_max), and with halo the
+// cells next to tile ends are copied on the way.  Frozen problems keep their
+// last dt.
 __global__ __launch_bounds__(256) void batch_dt_kernel(const double* U, int64_t total,
                                                        const int64_t* offsets,
                                                        const double* dx, double cfl,
@@ -33,7 +38,7 @@ __global__ __launch_bounds__(256) void batch_dt_kernel(const double* U, int64_t 
   const int p = blockIdx.x;
   const int act = pstatus[p] == ST_OK;
   if (threadIdx.x == 0) active[p] = act;
-  if (!act || !(cfl > 0.0 || halo)) return;
+  if (!act || !(cfl > 0.0)) return;
   const int64_t lo = offsets[p], n = offsets[p + 1] - lo;
   double m = 0.0;
   for (int64_t l = threadIdx.x; l < n; l += blockDim.x) {
@@ -61,7 +66,6 @@ __global__ __launch_bounds__(256) void batch_dt_kernel(const double* U, int64_t 
     const double s = (fabs(q[1]) + cs) / dx[p];
     m = (s > m || s != s) ? s : m;
   }
-  if (!(cfl > 0.0)) return;
   __shared__ double red[256];
   red[threadIdx.x] = m;
   __syncthreads();
@@ -77,6 +81,35 @@ __global__ __launch_bounds__(256) void batch_dt_kernel(const double* U, int64_t 
     if (dt_max > 0.0 && h > dt_max) h = dt_max;
     dt[p] = h;
   }
+}
+
+// The copies of the cells next to tile ends alone, a group of 32 lanes per
+// tile; the groups of problems' first tiles write active.  With fixed time
+// steps there is nothing else to do at the start of a step (the kernel above
+// walks every cell, one workgroup a problem: 8 tubes of 200 000 cells, float,
+// 534 us a step, 58 so).
+constexpr int kEdgeLanes = 32;
+__global__ __launch_bounds__(256) void batch_edges_kernel(const double* U, int64_t total,
+                                                          const int64_t* offsets,
+                                                          const int64_t* tstart,
+                                                          const int32_t* tprob, int64_t ntiles,
+                                                          const int32_t* pstatus, int32_t* active,
+                                                          int tc, double* halo) {
+  const int64_t t = (int64_t)blockIdx.x * (256 / kEdgeLanes) + threadIdx.x / kEdgeLanes;
+  const int k = threadIdx.x % kEdgeLanes;
+  if (t >= ntiles) return;
+  const int p = tprob[t];
+  const int64_t lo = offsets[p], hi = offsets[p + 1], c0 = tstart[t];
+  if (k == 0 && c0 == lo) active[p] = pstatus[p] == ST_OK;
+  if (k >= 2 * kHalo) return;
+  const int64_t c1 = c0 + tc < hi ? c0 + tc : hi;
+  const int64_t cell = k < kHalo ? c0 - kHalo + k : c1 + (k - kHalo);
+  if (cell < lo || cell >= hi) return;
+  double u[5];
+#pragma unroll
+  for (int c = 0; c < 5; c++) u[c] = U[c * total + cell];
+#pragma unroll
+  for (int c = 0; c < 5; c++) halo[(t * 2 * kHalo + k) * 5 + c] = u[c];
 }
 
 static hipError_t launch_batch_stage(int precision, int tl, const BatchArgs& a, int mode,
@@ -97,6 +130,13 @@ static hipError_t launch_batch_step(int precision, int nthr, const BatchArgs& a,
 // ---------------------------------------------------------------------------
 static const int kTiles[] = {63, 127, 255};
 static const int kBlocksPerCU[] = {2, 4, 8, 16};
+// Cells of a plan's longest problem from which batch_edges_kernel runs beside
+// the start kernel instead of in it.  A problem is one workgroup's walk there
+// and the copies lengthen it by about 0.46 us per 1000 cells, against about 1.5
+// us for one more launch: 2 tubes of 500 000 cells 1250 us a step in one kernel
+// and 1017 apart, 50 of 3000 to 9000 80 and 77, 100 of 2000 to 6000 92 and 90
+// (float 56.0 and 56.3), 300 of 50 to 1500 82 and 83.
+static const int64_t kLongWalk = 8192;
 
 struct TileTable {
   int64_t* start = nullptr;
@@ -110,6 +150,7 @@ struct isweno_batch_plan {
   int device = 0;
   int ncu = 256;
   int32_t nprob = 0;
+  int64_t longest = 0;         // cells of the longest problem
   int64_t total = 0;
   int32_t bc_lo = 0, bc_hi = 0;
   int64_t* offsets = nullptr;  // device
@@ -189,17 +230,29 @@ static int check_batch_opts(const isweno_opts* o) {
   return ISWENO_OK;
 }
 
-// Enqueue one RK3 step (dt kernel + three persistent stages) on s.
+// Enqueue one RK3 step on s: the start-of-step kernel, then the step kernel, or
+// three persistent stages with a periodic end.
 static hipError_t enqueue_step(isweno_batch_plan* p, const isweno_opts* o, double* U, double* dt,
                                isweno_stats* stats, int32_t* pstatus, int tl, int bpc,
                                hipStream_t s) {
   const TileTable& t = p->tables[tl];
-  {
+  const int tc = isw::step_tile(tl + 1);
+  // Whole steps: the copies next to tile ends in a kernel of their own where
+  // there is no time step to form or a problem is long (kLongWalk)
+  const bool edges = whole_steps(p) && (!(o->cfl > 0.0) || p->longest > kLongWalk);
+  hipError_t e;
+  if (!edges || o->cfl > 0.0) {
     hipLaunchKernelGGL(isw::batch_dt_kernel, dim3(p->nprob), dim3(256), 0, s, U, p->total,
-                       p->offsets, p->dx, o->cfl, o->dt_max, dt, pstatus, p->active,
-                       isw::step_tile(tl + 1), t.first, t.halo);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+                       p->offsets, p->dx, o->cfl, o->dt_max, dt, pstatus, p->active, tc, t.first,
+                       edges ? nullptr : t.halo);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
+  if (edges) {
+    const int64_t groups = 256 / isw::kEdgeLanes;
+    hipLaunchKernelGGL(isw::batch_edges_kernel, dim3((unsigned)((t.ntiles + groups - 1) / groups)),
+                       dim3(256), 0, s, U, p->total, p->offsets, t.start, t.prob, t.ntiles, pstatus,
+                       p->active, tc, t.halo);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   isw::BatchArgs a{};
   a.active = p->active;
@@ -229,7 +282,6 @@ static hipError_t enqueue_step(isweno_batch_plan* p, const isweno_opts* o, doubl
   const int blocks = (int)blocks64;
   double* U1 = p->ws;
   double* U2 = p->ws + 5 * p->total;
-  hipError_t e;
   a.Uin = U;
   a.Uout = U1;
   if ((e = isw::launch_batch_stage(o->precision, tl, a, isw::OUT_RK1, blocks, s)) != hipSuccess)
@@ -270,6 +322,8 @@ int isweno_batch_plan_create(isweno_ctx* ctx, int32_t nprob, const int64_t* offs
   p->bc_lo = bc_lo;
   p->bc_hi = bc_hi;
   p->host_offsets.assign(offsets, offsets + nprob + 1);
+  for (int32_t q = 0; q < nprob; q++)
+    p->longest = std::max(p->longest, offsets[q + 1] - offsets[q]);
   bool ok = hipMalloc(&p->offsets, sizeof(int64_t) * (nprob + 1)) == hipSuccess &&
             hipMalloc(&p->dx, sizeof(double) * nprob) == hipSuccess &&
             (whole_steps(p) ||

@@ -346,11 +346,6 @@ __global__ __launch_bounds__(NTHR, 4) void batch_step_kernel(BatchArgs g) {
   }
 }
 
-// Start of a step, one workgroup per problem: a problem is advanced in this
-// step when its status is still OK (active[p]); then, when cfl > 0,
-// dt[p] = cfl / max_cells (|u| + c)/dx_p (clipped to dt_max).  Frozen
-// problems keep their last dt.
-
 template <typename T, int TL, bool CUT>
 static hipError_t launch_stage_c(const BatchArgs& a, int mode, int blocks, hipStream_t s) {
   if (mode == OUT_RK1)
