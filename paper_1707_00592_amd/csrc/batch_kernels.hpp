@@ -32,6 +32,7 @@ struct BatchArgs {
   double eps;
   double* U;               // whole steps: the state, advanced in place
   const double* halo;      // whole steps: kHalo cells each side of every tile
+  int64_t tile0;           // whole steps: the launch's first tile
 };
 
 // Cells a whole step of a tile reads beyond each of its ends: three stages of
@@ -198,7 +199,7 @@ __global__ __launch_bounds__(NTHR, 4) void batch_step_kernel(BatchArgs g) {
   __shared__ double su[NC * NTHR];
   __shared__ TileNotes<NTHR / 64> s_notes[2];
   const int tid = threadIdx.x;
-  const int64_t t = blockIdx.x;
+  const int64_t t = g.tile0 + blockIdx.x;
   const int prob = g.tprob[t];
   if (!g.active[prob]) return;  // non-physical when this step began (the same for every lane)
   const int64_t lo = g.offsets[prob], n = g.offsets[prob + 1] - lo;
@@ -385,14 +386,22 @@ static hipError_t launch_stage_t(int tl, const BatchArgs& a, int mode, int block
 // Whole steps: nthr lanes per tile of step_tile(nthr) cells.
 template <typename T, int NTHR>
 static hipError_t launch_step_n(const BatchArgs& a, hipStream_t s) {
-  if (a.ntiles < 1 || a.ntiles > 0x7fffffffLL) return hipErrorInvalidValue;
-  if (a.weights == W_CUTOFF)
-    hipLaunchKernelGGL((batch_step_kernel<T, NTHR, true>), dim3((unsigned)a.ntiles), dim3(NTHR), 0,
-                       s, a);
-  else
-    hipLaunchKernelGGL((batch_step_kernel<T, NTHR, false>), dim3((unsigned)a.ntiles), dim3(NTHR),
-                       0, s, a);
-  return hipGetLastError();
+  if (a.ntiles < 1) return hipErrorInvalidValue;
+  // a launch holds less than 2^32 lanes; tiles are independent (their
+  // neighbours' cells are copies), so more of them are more launches
+  constexpr int64_t kMost = 0xffffffffLL / NTHR;
+  BatchArgs b = a;
+  for (b.tile0 = 0; b.tile0 < a.ntiles; b.tile0 += kMost) {
+    const int64_t left = a.ntiles - b.tile0;
+    const dim3 grid((unsigned)(left < kMost ? left : kMost));
+    if (a.weights == W_CUTOFF)
+      hipLaunchKernelGGL((batch_step_kernel<T, NTHR, true>), grid, dim3(NTHR), 0, s, b);
+    else
+      hipLaunchKernelGGL((batch_step_kernel<T, NTHR, false>), grid, dim3(NTHR), 0, s, b);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 template <typename T>
