@@ -174,7 +174,11 @@ static void free_graphs(isweno_batch_plan* p) {
   p->graphs.clear();
 }
 
-// Whole steps in one launch: every plan but those with a periodic end.
+// Whole steps in one launch: every plan but those with a periodic end.  In
+// FP64 at the default lanes 20 tubes of 50 to 150 cells take 45 us a step where
+// one launch per stage took 46, 60 of 100 to 600 49 and 51, 1000 of 20 to 80 61
+// and 62, 300 of 50 to 1500 85 and 100, 4096 of 128 to 4096 1024 and 1790
+// (float 31 and 33, 33 and 36, 38 and 40, 48 and 59, 559 and 1090).
 static bool whole_steps(const isweno_batch_plan* p) {
   return p->bc_lo != ISWENO_BC_PERIODIC && p->bc_hi != ISWENO_BC_PERIODIC;
 }
@@ -324,6 +328,15 @@ int isweno_batch_plan_create(isweno_ctx* ctx, int32_t nprob, const int64_t* offs
   p->host_offsets.assign(offsets, offsets + nprob + 1);
   for (int32_t q = 0; q < nprob; q++)
     p->longest = std::max(p->longest, offsets[q + 1] - offsets[q]);
+  // Whole steps: the fewest lanes that hold every problem in one tile, else the
+  // most (1000 tubes of 20 to 80 cells: 128 lanes 61.3 us a step, 256 lanes
+  // 63.3).  The autotuner tries all.
+  if (whole_steps(p))
+    for (int tl : kTiles)
+      if (p->longest <= isw::step_tile(tl + 1)) {
+        p->tl = tl;
+        break;
+      }
   bool ok = hipMalloc(&p->offsets, sizeof(int64_t) * (nprob + 1)) == hipSuccess &&
             hipMalloc(&p->dx, sizeof(double) * nprob) == hipSuccess &&
             (whole_steps(p) ||

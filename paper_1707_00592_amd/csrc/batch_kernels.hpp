@@ -106,15 +106,22 @@ __global__ __launch_bounds__(TL + 1, sizeof(T) == 4 ? 6 : 1) void batch_stage_ke
     const TileState tile{!(notes & TILE_FAR) && eps_in_range(g.eps),
                          sizeof(T) == 8 && !(notes & TILE_FLUIDS)};
     const double h = g.dt[prob];
-    // the output step of a cell's component (offset o) from its L and the
-    // stage input there
-    auto put = [&](int64_t o, double L, auto uin) {
-      if (MODE == OUT_RK1) {
-        g.Uout[o] = g.U0[o] + h * L;
-      } else if (MODE == OUT_RK2) {
-        g.Uout[o] = 0.75 * g.U0[o] + 0.25 * (uin(o) + h * L);
-      } else {
-        g.Uout[o] = (1.0 / 3.0) * g.U0[o] + (2.0 / 3.0) * (uin(o) + h * L);
+    // the output step of a cell from its L; uin(c) is the stage input there.
+    // Everything is loaded before anything is stored (the compiler may not move
+    // a load over the store before it).
+    auto put = [&](int64_t cell, const double* L, auto uin) {
+      double u0[NC], ui[NC];
+#pragma unroll
+      for (int c = 0; c < NC; c++) {
+        u0[c] = g.U0[c * total + cell];
+        if (MODE != OUT_RK1) ui[c] = uin(c);
+      }
+#pragma unroll
+      for (int c = 0; c < NC; c++) {
+        const int64_t o = c * total + cell;
+        if (MODE == OUT_RK1) g.Uout[o] = u0[c] + h * L[c];
+        else if (MODE == OUT_RK2) g.Uout[o] = 0.75 * u0[c] + 0.25 * (ui[c] + h * L[c]);
+        else g.Uout[o] = (1.0 / 3.0) * u0[c] + (2.0 / 3.0) * (ui[c] + h * L[c]);
       }
     };
     // a uniform tile (steady_state): every face has the same flux
@@ -122,11 +129,11 @@ __global__ __launch_bounds__(TL + 1, sizeof(T) == 4 ? 6 : 1) void batch_stage_ke
       double q[NC];
       cons_prim<1, T>(ref, q);
       if (steady_state<T, 1>(q, g.eps)) {
-        for (int j = tid; j < len; j += NTHR)
+        double L[NC];
 #pragma unroll
-          for (int c = 0; c < NC; c++)
-            put(c * total + lo + l0 + j, steady_term(c >= 3, q[c]),
-                [&](int64_t) { return ref[c]; });
+        for (int c = 0; c < NC; c++) L[c] = steady_term(c >= 3, q[c]);
+        for (int j = tid; j < len; j += NTHR)
+          put(lo + l0 + j, L, [&](int c) { return ref[c]; });
         __syncthreads();  // the notes are reused by the next tile
         continue;
       }
@@ -161,9 +168,8 @@ __global__ __launch_bounds__(TL + 1, sizeof(T) == 4 ? 6 : 1) void batch_stage_ke
       }
       dx.template quotients<NC + 2>(x);
 #pragma unroll
-      for (int k = 0; k < NC; k++)
-        put(k * total + cell, k >= 3 ? x[k] + x[k + 2] : x[k],
-            [&](int64_t o) { return g.Uin[o]; });
+      for (int k = 3; k < NC; k++) x[k] = x[k] + x[k + 2];
+      put(cell, x, [&](int c) { return g.Uin[c * total + cell]; });
     }
     __syncthreads();  // LDS is reused by the next tile
   }
@@ -332,9 +338,13 @@ __global__ __launch_bounds__(NTHR, 4) void batch_step_kernel(BatchArgs g) {
       if (k >= 3) x[k + 2] = double(T(su[k * NTHR + tid])) * (usr - us);
     }
     dx.template quotients<NC + 2>(x);
+    // (U^n of every component before the first store, as the stage launches)
+    double v0[NC];
+#pragma unroll
+    for (int k = 0; k < NC; k++) v0[k] = stage == 0 ? su[k * NTHR + tid] : un(k, mine);
 #pragma unroll
     for (int k = 0; k < NC; k++) {
-      const double u = su[k * NTHR + tid], u0 = stage == 0 ? u : un(k, mine);
+      const double u = su[k * NTHR + tid], u0 = v0[k];
       const double r = k >= 3 ? x[k] + x[k + 2] : x[k];
       if (stage == 0) su[k * NTHR + tid] = u0 + h * r;
       else if (stage == 1) su[k * NTHR + tid] = 0.75 * u0 + 0.25 * (u + h * r);
