@@ -16,6 +16,7 @@
 #include "batch_kernels.hpp"
 
 #include <algorithm>
+#include <iterator>
 #include <map>
 #include <new>
 #include <tuple>
@@ -431,6 +432,19 @@ int isweno_batch_autotune(isweno_ctx* ctx, isweno_batch_plan* p, const isweno_op
   p->blocks_per_cu = best_bpc;
   if (chosen_tile) *chosen_tile = best_tl;
   return ISWENO_OK;
+}
+
+// Not part of the ABI (isweno.h does not declare it): the tests compare every
+// lane count with the oracle, which the autotuner's timing would leave to chance.
+ISWENO_API int isweno_test_batch_lanes(isweno_batch_plan* p, int32_t lanes) {
+  if (!p || std::find(std::begin(kTiles), std::end(kTiles), lanes - 1) == std::end(kTiles))
+    return ISWENO_ERR_ARG;
+  if (hipSetDevice(p->device) != hipSuccess || hipDeviceSynchronize() != hipSuccess)
+    return ISWENO_ERR_DEVICE;
+  free_graphs(p);
+  const int r = build_table(p, lanes - 1);
+  if (r == ISWENO_OK) p->tl = lanes - 1;
+  return r;
 }
 
 int isweno_batch_step(isweno_ctx* ctx, isweno_batch_plan* p, const isweno_opts* o, double* U,
