@@ -40,8 +40,10 @@ FACE_OPS = {1: 1160, 2: 1269, 3: 1378}
 # A reconstruction that takes its shortcut (FP64: tau5 of eq. (25) so far
 # below epsilon that the weights are exactly d_k: candidates 16, tau5 15,
 # combination 7, the test 1 = 39 of the 101 operations; FP32 form: a flat
-# stencil, its spread 8 operations) saves the difference.  Uniform tiles,
-# which evaluate no face, count as faces whose every reconstruction took it.
+# stencil, its spread 8 operations) saves the difference.  Tiles that hold one
+# state evaluate no face (their field-sides are among those counted as
+# shortcuts): the faces and cell updates of such tiles are taken out whole, as
+# the mean of the states before and after the timed steps has them.
 SHORTCUT_SAVING_F64 = 101 - 39
 SHORTCUT_SAVING_F32 = 101 - 8
 PRIM_OPS = {1: 7, 2: 10, 3: 13}
@@ -438,6 +440,7 @@ def run_form(isweno, ctx, p, U0, opts, steps, warmup, torch, kernel_steps=None):
     sk = isweno.new_stats()
     for _ in range(warmup):
         ctx.rk3_step(Uk, grid, opts, dk, sk)
+    before = Uk.clone()
     ctx.timing_enable(True)
     torch.cuda.synchronize()
     t1 = time.perf_counter()
@@ -457,8 +460,48 @@ def run_form(isweno, ctx, p, U0, opts, steps, warmup, torch, kernel_steps=None):
                 # the fused 2D stage counts its x and y field-sides per axis
                 kern[name]["shortcuts_per_launch"] = (shortcuts[0] + shortcuts[1]) / n
     ctx.timing_enable(False)
-    del Uk
+    uniform_work(kern, p, before, Uk, torch)
+    del Uk, before
     return U, el, kern, stats, {"steps": ks, "ms_per_step": el_direct / ks * 1e3}
+
+
+# Cells of a tile of the fused 2D stage (csrc/stage2d_kernel.hpp).
+STAGE2D_TILE = (15, 16)
+
+
+def uniform_tiles_2d(U, p, torch):
+    """(faces, cells) of the fused 2D stage's tiles whose every cell, with the
+    three beyond each end, holds one state."""
+    nx, ny = p.n
+    tx, ty = STAGE2D_TILE
+    Q = U.view(torch.int64).reshape(6, ny, nx)
+
+    def integral(d):  # d[y, x] != 0: sums over rectangles from its corner
+        return torch.nn.functional.pad(d.double().cumsum(0).cumsum(1), (1, 0, 1, 0))
+
+    # a region is uniform when no two neighbours in it differ
+    dx = integral((Q[:, :, 1:] != Q[:, :, :-1]).any(0))
+    dy = integral((Q[:, 1:, :] != Q[:, :-1, :]).any(0))
+    x0 = torch.arange(0, nx, tx, device=U.device)
+    y0 = torch.arange(0, ny, ty, device=U.device)
+    x1, y1 = (x0 + tx).clamp(max=nx), (y0 + ty).clamp(max=ny)
+
+    def differ(S, ya, yb, xa, xb):
+        return S[yb][:, xb] - S[ya][:, xb] - S[yb][:, xa] + S[ya][:, xa]
+
+    same = (differ(dx, y0, y1, (x0 - 3).clamp(min=0), (x1 + 2).clamp(max=nx - 1)) == 0) & \
+        (differ(dy, (y0 - 3).clamp(min=0), (y1 + 2).clamp(max=ny - 1), x0, x1) == 0)
+    w, h = (x1 - x0)[None, :], (y1 - y0)[:, None]
+    faces = (w + (x1 == nx)[None, :]) * h + (h + (y1 == ny)[:, None]) * w
+    return int((faces * same).sum()), int((w * h * same).sum())
+
+
+def uniform_work(kern, p, before, after, torch):
+    """Adds the uniform tiles' faces and cells to the fused 2D stage's entry."""
+    if "stage_2d" in kern:
+        ends = [uniform_tiles_2d(V, p, torch) for V in (before, after)]
+        kern["stage_2d"]["uniform_faces"], kern["stage_2d"]["uniform_cells"] = (
+            sum(e[i] for e in ends) / 2 for i in (0, 1))
 
 
 def kernel_work(name, p):
@@ -524,6 +567,7 @@ def full_run(isweno, ctx, p, U0, opts, steps, torch):
             elif k == isweno.K_STAGE2D:
                 kern[name]["shortcuts_per_launch"] = (shortcuts[0] + shortcuts[1]) / n
     ctx.timing_enable(False)
+    uniform_work(kern, p, U0, Uk, torch)
     same = bool(torch.equal(U, Uk))
     del Uk
     return U, el, kern, stats, same
@@ -540,7 +584,10 @@ def roofline(kern, p, precision, with_traffic=False):
     # reconstructions that took their shortcut did less work
     sc = k.get("shortcuts_per_launch", 0.0)
     saving = SHORTCUT_SAVING_F64 if precision == "f64" else SHORTCUT_SAVING_F32
-    flops -= sc * saving
+    uf, uc = k.get("uniform_faces", 0.0), k.get("uniform_cells", 0.0)
+    whole = flops
+    flops -= (sc - uf * 2 * nc) * saving + uf * FACE_OPS[p.ndim]
+    flops -= uc * sum(axis_ops(p.ndim, D) for D in axes)
     sec = k["avg_ms"] * 1e-3
     achieved = flops / sec / 1e12
     peak = PEAK["f64_valu_tflops"] if precision == "f64" else PEAK["f32_valu_tflops"]
@@ -555,7 +602,8 @@ def roofline(kern, p, precision, with_traffic=False):
            "flops_per_launch": int(flops), "avg_launch_ms": round(k["avg_ms"], 4),
            "launches": k["launches"],
            "shortcut_fraction": round(sc / (faces * 2 * nc), 4),
-           "flops_per_launch_without_shortcuts": int(flops + sc * saving),
+           "uniform_face_fraction": round(uf / faces, 4),
+           "flops_per_launch_without_shortcuts": int(whole),
            "hbm_at_traffic_gbs": None if traffic is None else round(traffic / sec / 1e9, 1)}
     if hbm is not None:
         out["hbm_algorithmic_gbs"] = round(hbm / sec / 1e9, 1)

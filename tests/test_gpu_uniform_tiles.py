@@ -160,3 +160,27 @@ def test_epsilon_zero_batch(lib, ctx, bc):
     assert _same_bits(V.cpu().numpy(), ref)
     got = lib.read_stats(st)
     assert (got.o3[0], got.o1[0]) == (so.o3[0], so.o1[0]) and so.o1[0] > 0
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+@pytest.mark.parametrize("which", range(len(STATES)))
+def test_status_and_steps_match_the_oracle(lib, ctx, shape, which):
+    """Step by step, the status first: a failure that only one side latches is
+    an error, not a reason to compare nothing."""
+    import torch
+    d = len(shape)
+    dx = tuple(1.0 / m for m in shape)
+    og, ig = oracle.make_grid(shape, dx, (0,) * d, (0,) * d), lib.make_grid(shape, dx, 0, 0)
+    for k in range(2):
+        W = _uniform(shape, STATES[which], k)
+        if k:
+            W[:, W.shape[1] // 3] *= 1 + 1e-9
+        U, st = _dev(W), lib.new_stats()
+        dt = torch.zeros(1, dtype=torch.float64, device="cuda")
+        for step in range(3):
+            ctx.rk3_step(U, ig, lib.make_opts(), dt, st)
+            W, s = oracle.rk3_step(W, og, oracle.cfl_dt(W, og, oracle.make_opts()), oracle.make_opts())
+            assert lib.read_stats(st).status == s, (k, step)
+            if s != 0:
+                break
+            assert _same_bits(U.cpu().numpy(), W), (k, step)
