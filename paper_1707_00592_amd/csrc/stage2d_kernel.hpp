@@ -49,8 +49,9 @@ struct LdsStencil2 {
 
 // At least 4 resident waves per SIMD (registers capped at 128).  The
 // cut-off weights with the gathered cascade need more (about 250 in FP64)
-// and get 2.
-template <typename T, int MODE, bool CUT, bool GATHER>
+// and get 2.  LOOK: whether uniform tiles and tiles of one fluid are told
+// apart (kLookTiles).
+template <typename T, int MODE, bool CUT, bool GATHER, bool LOOK>
 __global__ __launch_bounds__(kThreads, CUT && GATHER ? 2 : 4) void stage2d_kernel(SweepArgs g) {
   constexpr int NDIM = 2, NC = 6, TX = kTX, TY = kTY, NTHR = kThreads;
   constexpr int SX = kSX, QROW = kQROW;
@@ -116,7 +117,7 @@ __global__ __launch_bounds__(kThreads, CUT && GATHER ? 2 : 4) void stage2d_kerne
   __builtin_amdgcn_s_setprio(1);
   // 1. stage primitives: the tile's interior cells, its rows extended by 3
   // cells each way along x and its columns by 3 each way along y
-  int found = skip ? TILE_SKIP : 0;
+  int found = (skip ? TILE_SKIP : 0) | (LOOK ? 0 : TILE_MIXED | TILE_FLUIDS);
   double m = 0.0, h1 = 0.0;  // SPEEDS: the lane's max wave speed; FROM_L: dt
   if constexpr (FROM_L) h1 = *g.dt;
   const double dxs[2] = {g.dx[0], g.dx[1]};
@@ -129,7 +130,7 @@ __global__ __launch_bounds__(kThreads, CUT && GATHER ? 2 : 4) void stage2d_kerne
     }
   };
   double ref[NC];
-  input(gy0 * nx + gx0, ref);
+  if constexpr (LOOK) input(gy0 * nx + gx0, ref);
   for (int e = tid; e < QROW; e += NTHR) {
     const int yy = e / SX, xx = e % SX;
     const int64_t gxl = gx0 + xx - 3, gyl = gy0 + yy - 3;
@@ -145,7 +146,7 @@ __global__ __launch_bounds__(kThreads, CUT && GATHER ? 2 : 4) void stage2d_kerne
     const int64_t cell = iy * nx + ix;
     double u[NC], q[NC];
     input(cell, u);
-    found |= differs<NC, true>(u, ref, flip);
+    if constexpr (LOOK) found |= differs<NC, true>(u, ref, flip);
     cons_prim<NDIM, T>(u, q);
     const bool inr = sizeof(T) == 8 && in_range<NDIM>(q);
     if constexpr (sizeof(T) == 8) found |= inr ? 0 : TILE_FAR;
@@ -183,7 +184,7 @@ __global__ __launch_bounds__(kThreads, CUT && GATHER ? 2 : 4) void stage2d_kerne
 
   int my3[2] = {0, 0}, my1[2] = {0, 0}, mys[2] = {0, 0};
   const int wts = kernel_weights<CUT>(g.weights);
-  const TileState tile{!(notes & TILE_FAR) && eps_in_range(g.eps), !(notes & TILE_FLUIDS)};
+  const TileState tile{!(notes & TILE_FAR) && eps_in_range(g.eps), LOOK && !(notes & TILE_FLUIDS)};
   const int cy = tid >> 4, cx = tid & 15;  // the lane's cell (cx < 15) and x face
   const bool mine = cx < TX && gx0 + cx < nx && gy0 + cy < ny;
   const int64_t mycell = (gy0 + cy) * nx + gx0 + cx;
@@ -213,7 +214,7 @@ __global__ __launch_bounds__(kThreads, CUT && GATHER ? 2 : 4) void stage2d_kerne
     }
   };
   // a uniform tile (steady_state): every face has the same flux
-  if (!(notes & TILE_MIXED)) {
+  if (LOOK && !(notes & TILE_MIXED)) {
     double q[NC];
     cons_prim<NDIM, T>(ref, q);
     if (steady_state<T, NDIM>(q, g.eps)) {
@@ -459,6 +460,15 @@ __global__ __launch_bounds__(kThreads, CUT && GATHER ? 2 : 4) void stage2d_kerne
   }
 }
 
+// The float form looks for uniform tiles only where a CU has more than two
+// tiles to run.  Below, a stage takes as long as its slowest tile and the
+// comparison with the code behind it is 0.3 us of that (2D derivative 198 x 69
+// 11.7 us with it, 11.4 without; 429 x 104, a step 62.8 and 61.9); above, tiles
+// without faces make room (700 x 300, 893 tiles, at the start of a run 68.0 us
+// a step with it, 73.3 without; mixed states 98.7 and 97.7).  FP64 looks
+// everywhere: its faces gain from one_fluid at any size.
+constexpr int64_t kLookTiles = 512;
+
 template <typename T, int MODE, bool CUT, bool GATHER>
 static hipError_t launch_t(const SweepArgs& a, hipStream_t s, LaunchEvents ev) {
   // one workgroup per tile: the kernel maps block b to tile (b & 7, b >> 3)
@@ -470,11 +480,19 @@ static hipError_t launch_t(const SweepArgs& a, hipStream_t s, LaunchEvents ev) {
   if (blocks <= 0) return hipSuccess;
   if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
   const dim3 grid((unsigned)blocks), block(kThreads);
-  if (ev.start)
-    hipExtLaunchKernelGGL((stage2d_kernel<T, MODE, CUT, GATHER>), grid, block, 0, s, ev.start,
-                          ev.stop, 0, a);
-  else
-    hipLaunchKernelGGL((stage2d_kernel<T, MODE, CUT, GATHER>), grid, block, 0, s, a);
+  auto go = [&](auto kern) {
+    if (ev.start)
+      hipExtLaunchKernelGGL(kern, grid, block, 0, s, ev.start, ev.stop, 0, a);
+    else
+      hipLaunchKernelGGL(kern, grid, block, 0, s, a);
+  };
+  if constexpr (sizeof(T) == 4) {
+    if (blocks <= kLookTiles) {
+      go(stage2d_kernel<T, MODE, CUT, GATHER, false>);
+      return hipGetLastError();
+    }
+  }
+  go(stage2d_kernel<T, MODE, CUT, GATHER, true>);
   return hipGetLastError();
 }
 

@@ -184,3 +184,27 @@ def test_status_and_steps_match_the_oracle(lib, ctx, shape, which):
             if s != 0:
                 break
             assert _same_bits(U.cpu().numpy(), W), (k, step)
+
+
+@pytest.mark.parametrize("shape", [(300, 409), (301, 417), (420, 410)])
+@pytest.mark.parametrize("mood", [1, 2])
+def test_float_form_on_both_sides_of_the_tile_count(lib, ctx, shape, mood):
+    """520 and 480, 567 and 504, 728 and 672 tiles: the float form tells uniform
+    tiles apart beyond 512.  A uniform state keeps the FP64 form's signed zeros,
+    one with a pressure bump its derivative within 1e-3 (relative L1: fluxes are
+    rounded to float, 6e-8, and differ by percents across the bump) and zeros
+    away from it."""
+    for ny in (shape[1], shape[1] - 40):
+        n = (shape[0], ny)
+        ig = lib.make_grid(n, (0.01, 0.01), 0, 0)
+        U = _uniform(n, STATES[1], 1)
+        a, b = (ctx.rhs(_dev(U), ig, lib.make_opts(precision=p, mood=mood)).cpu().numpy()
+                for p in (0, 1))
+        assert _same_bits(a, b)
+        x, y = np.meshgrid(np.arange(n[0]), np.arange(n[1]))
+        r2 = ((x - 100) ** 2 + (y - 120) ** 2).ravel()
+        U[3] *= 1 + 0.1 * np.maximum(0, 1 - r2 / 400.0)
+        a, b = (ctx.rhs(_dev(U), ig, lib.make_opts(precision=p, mood=mood)).cpu().numpy()
+                for p in (0, 1))
+        assert np.abs(b - a).sum() <= 1e-3 * np.abs(a).sum()
+        assert (b[:, r2 > 26 ** 2] == 0).all() and (b[:, r2 < 16 ** 2] != 0).any()
