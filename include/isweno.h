@@ -254,10 +254,11 @@ ISWENO_API int isweno_batch_autotune(isweno_ctx *ctx, isweno_batch_plan *plan,
  * values are then unspecified) and the problem is not advanced afterwards,
  * while the other problems go on.  stats (may be NULL) gets the MOOD
  * counters and, when any problem failed, ISWENO_ERR_NONPHYSICAL.  Each step
- * is one HIP graph launch (a per-problem start-of-step kernel, then one kernel
- * that carries every tile through the step; with a periodic end three
- * persistent stage kernels), instantiated on first use for this (plan, U,
- * dt, stats, status, opts) and replayed afterwards. */
+ * is one HIP graph launch (a per-problem start-of-step kernel, or one over
+ * tiles with given dt, or both with long problems; then one kernel that
+ * carries every tile through the step, or three persistent stage kernels with
+ * a periodic end), instantiated on first use for this (plan, U, dt, stats,
+ * status, opts) and replayed afterwards. */
 ISWENO_API int isweno_batch_step(isweno_ctx *ctx, isweno_batch_plan *plan,
                       const isweno_opts *opts, double *U, double *dt,
                       int32_t nsteps, isweno_stats *stats, int32_t *status,

@@ -186,11 +186,12 @@ __global__ __launch_bounds__(TL + 1, sizeof(T) == 4 ? 6 : 1) void batch_stage_ke
 // stage pays its own launch, staging and last round of workgroups.  Here a
 // workgroup carries its tile through the three stages in registers and LDS,
 // evaluating the 6 (3) cells beyond each end in the first (second) stage
-// itself: 5% more faces at 256 lanes, a quarter of the bytes (4096 tubes of
-// 128 to 4096 cells: 1045 us a step against three stages of 450; 300 tubes of
-// 50 to 1500 cells, float: 30 us against three of 14).  The U^n of the
-// kHalo cells beyond its ends come from copies that the start-of-step kernel
-// made, so that neighbours may already have written theirs.  Ends of a
+// itself: 5% more faces at 256 lanes, 11% at 128, 25% at 64, and a quarter of
+// the bytes (4096 tubes of 128 to 4096 cells with the present faces: 1024 us a
+// step against 1320 in three stage launches; 300 tubes of 50 to 1500 cells 85
+// against 105, float 48 against 57).  The U^n of the kHalo cells beyond its
+// ends come from copies made at the start of the step, so that neighbours may
+// already have written theirs.  Ends of a
 // problem: ghosts of a stage are written by the lanes that hold the cells they
 // mirror (not for periodic ends, whose neighbours are another tile's).
 // Lane tid holds cell l0 - 6 + tid and the face to its left; staged position p

@@ -283,9 +283,10 @@ __device__ __forceinline__ double weno_f64_fast(double a, double b, double c, do
 //
 // What is left out.  A product by 2, 4 or 1/4 is exact, so the add it feeds
 // may be one fused multiply-add: 27 instead of 37 instructions for the
-// indicators and 12 instead of 15 for tau5.  The range check of the shared reciprocals is not made on the
-// indicators of every stencil but once per tile on its cells (in_range) and
-// once per face on the sound speed (kFaceC2Min): with rho in [2^-20, 2^30],
+// indicators and 12 instead of 15 for tau5.  The range check of the shared
+// reciprocals is not made on the indicators of every stencil but once per tile
+// on its cells (in_range) and once per face on the sound speed (kFaceC2Min):
+// with rho in [2^-20, 2^30],
 // |u| <= 2^24, |p|, |Pi| <= 2^40, Gamma in [2^-10, 2^10] and c^2 >= 2^-40 a
 // characteristic value is at most 2^94 (acoustic: rho c u / 2) and the six
 // indicators together below 2^200.  From below nothing is left to check: the

@@ -299,8 +299,9 @@ __device__ __forceinline__ bool c2_positive(const double* q) {
 // [2^-10, 2^16] and the Mach number below 2^6 -- a rounding of 2^-24 then
 // moves no reconstructed density or stiff pressure by more than 2^-12 of it.
 // Such a tile costs its loads and stores (1024x512 at the start of a run, nine
-// tenths of it uniform: 45 us a stage against 69; fully mixed states pay one
-// comparison per staged cell, below what two runs differ by).
+// tenths of it uniform: 35 us a stage against 69); mixed states pay one
+// comparison per staged cell, which shows only in float stages of some 10 us
+// (kLookTiles).
 // FP64 with epsilon = 0 is left to the faces: a constant stencil's weights
 // are 0/0 there, and its tile's NaNs and fallbacks are the method's (the float
 // form's flat stencils return their centre value whatever epsilon is).
