@@ -329,15 +329,14 @@ int isweno_batch_plan_create(isweno_ctx* ctx, int32_t nprob, const int64_t* offs
   p->host_offsets.assign(offsets, offsets + nprob + 1);
   for (int32_t q = 0; q < nprob; q++)
     p->longest = std::max(p->longest, offsets[q + 1] - offsets[q]);
-  // Whole steps: the fewest lanes that hold every problem in one tile, else the
-  // most (1000 tubes of 20 to 80 cells: 128 lanes 61.3 us a step, 256 lanes
-  // 63.3).  The autotuner tries all.
-  if (whole_steps(p))
-    for (int tl : kTiles)
-      if (p->longest <= isw::step_tile(tl + 1)) {
-        p->tl = tl;
-        break;
-      }
+  // The fewest lanes that hold every problem in one tile, else the most (1000
+  // tubes of 20 to 80 cells: 128 lanes 61.3 us a step, 256 lanes 63.3,
+  // float with periodic ends 41.5 and 42.8).  The autotuner tries all.
+  for (int tl : kTiles)
+    if (p->longest <= (whole_steps(p) ? isw::step_tile(tl + 1) : tl)) {
+      p->tl = tl;
+      break;
+    }
   bool ok = hipMalloc(&p->offsets, sizeof(int64_t) * (nprob + 1)) == hipSuccess &&
             hipMalloc(&p->dx, sizeof(double) * nprob) == hipSuccess &&
             (whole_steps(p) ||

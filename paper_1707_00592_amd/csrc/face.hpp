@@ -234,7 +234,10 @@ __device__ __forceinline__ double weno_f64_shared_recip(const Ind<double>& s, do
 // zero, or below 2^-60 epsilon (epsilon > 0).  Every ratio tau5/(beta +
 // epsilon) of eqs. (21) and (28) is then below 2^-59, 1 + ratio rounds to 1,
 // every weight is exactly d_k and the normalisation divides by the same sum on
-// every such stencil.  One rule for every path that counts or takes it.
+// every such stencil.  The rule by which such stencils are counted on every
+// path; the common form takes the linear form by it, the general one for tau5 =
+// 0 alone (the same bits; the wider branch cost the cut-off stage up to 30%
+// where epsilon is out of range).
 __device__ __forceinline__ bool linear_f64(double tau, double eps) {
   return eps > 0.0 && (tau == 0.0 || tau < 0x1p-60 * eps);
 }
@@ -258,19 +261,20 @@ __device__ __forceinline__ double weno_f64_linear(double a, double b, double c, 
          (ISW_D4 / s5) * c4;
 }
 
-// FP64 reconstruction of a face in general: stencils of the linear scheme
-// (linear_f64) take its form (no other indicator is needed); the others the
+// FP64 reconstruction of a face in general: stencils with tau5 = 0 take the
+// linear form (no other indicator is needed); the others the
 // shared-reciprocal form, recomputed with the plain divisions (weno_f64) on
 // the lanes outside its range.  The branches diverge per lane; a wave skips
-// a branch no lane needs.  nlin counts the stencils of the linear form.
+// a branch no lane needs.  nlin counts the stencils of linear_f64.
 __device__ __forceinline__ double weno_f64_fast(double a, double b, double c, double d,
                                                 double e, int weights, double eps,
                                                 bool order3, int& nlin) {
-  if (linear_f64(tau5<double>(a, b, c, d, e), eps)) {
+  if (eps > 0.0 && tau5<double>(a, b, c, d, e) == 0.0) {
     nlin++;
     return weno_f64_linear(a, b, c, d, e, order3);
   }
   const Ind<double> s = indicators<double>(a, b, c, d, e);
+  nlin += linear_f64(s.tau, eps) ? 1 : 0;
   double q = weno_f64_shared_recip(s, a, b, c, d, e, weights, eps, order3);
   if (!(eps >= 0x1p-200 && eps <= 0x1p100 && fast_division_range(s)))
     q = weno_f64(a, b, c, d, e, weights, eps, order3);
@@ -529,8 +533,8 @@ __device__ __forceinline__ int cut_mask_f64(const Ind<double>& s, double eps, bo
   return (p1 >= th ? 1 : 0) | (p2 >= th ? 2 : 0) | (p3 >= th ? 4 : 0) | (p4 >= th ? 8 : 0);
 }
 
-// The same for the cut-off weights.  Stencils of the linear scheme
-// keep every candidate (every ratio is next to zero) and take the weights of
+// The same for the cut-off weights.  Stencils with
+// tau5 = 0 keep every candidate (every ratio is zero) and take the weights of
 // the full set as compile-time constants.  The others take the FAST mask;
 // lanes outside its range redo the whole reconstruction with the plain
 // divisions (a separate path, as in weno_f64_fast, keeps the common path's
@@ -538,7 +542,7 @@ __device__ __forceinline__ int cut_mask_f64(const Ind<double>& s, double eps, bo
 __device__ __forceinline__ double weno_f64_cutoff(double a, double b, double c, double d,
                                                   double e, double eps, bool order3,
                                                   int& nlin) {
-  if (linear_f64(tau5<double>(a, b, c, d, e), eps)) {
+  if (eps > 0.0 && tau5<double>(a, b, c, d, e) == 0.0) {
     nlin++;
     constexpr CutWeights W = make_cut_weights();
     const double c1 = (1.0 / 2.0) * c + (1.0 / 2.0) * d;
@@ -549,6 +553,7 @@ __device__ __forceinline__ double weno_f64_cutoff(double a, double b, double c, 
     return ((W.w[15][0] * c1 + W.w[15][1] * c2) + W.w[15][2] * c3) + W.w[15][3] * c4;
   }
   const Ind<double> s = indicators<double>(a, b, c, d, e);
+  nlin += linear_f64(s.tau, eps) ? 1 : 0;
   double q = cut_combine(cut_mask_f64<true>(s, eps, order3), a, b, c, d, e, order3);
   if (!(eps >= 0x1p-200 && eps <= 0x1p100 && fast_division_range(s)))
     q = cut_combine(cut_mask_f64<false>(s, eps, order3), a, b, c, d, e, order3);
